@@ -6,7 +6,7 @@
 //      workgroup staged with coalesced channel-major loads, and interpolates,
 //   3. takes the signed k-th root y = sign(s)|s|^(1/k)       (Eq. 2, Eqs. 4-6),
 //   4. accumulates the power sums p_j = sum y^j, j = 1..k, with compensated
-//      float32 summation (pairwise groups of four, Kahan steps per 32 elements),
+//      float32 summation (groups of four, Kahan steps per 32 elements),
 // and per pixel recovers the order-k symmetric sum e_k from p_1..p_k with
 // Newton's identities (the general form of Eqs. 3, 7, 8 and 9):
 //   e_0 = 1,  m e_m = sum_{j=1..m} (-1)^(j-1) e_{m-j} p_j.
@@ -74,10 +74,6 @@ template <> struct Storage<HODMAS_I16> { using T = short; };
 // no swizzle; with stride 0 an access is in range iff its byte offset is below
 // the resource's size.
 constexpr int kBufferFlags = 0x00020000;
-
-__device__ __forceinline__ float widen(float v) { return v; }
-__device__ __forceinline__ float widen(_Float16 v) { return (float)v; }
-__device__ __forceinline__ float widen(short v) { return (float)v; }
 
 // Kahan step: s + x with the running compensation c (true sum ~ s - c).
 __device__ __forceinline__ void kahan_add(float& s, float& c, float x)
@@ -201,62 +197,48 @@ __device__ __forceinline__ float interp(const Tap& p, float s0, float s1)
     }
 }
 
+// The K-th root of a = |v|: square roots for K = 2 and 4, else 2^(log2 a / K),
+// where a = 0 gives 2^-inf = 0; and its square.
+template <int K>
+__device__ __forceinline__ float root(float a)
+{
+    if constexpr (K == 1)
+        return a;
+    else if constexpr (K == 2)
+        return __builtin_amdgcn_sqrtf(a);
+    else if constexpr (K == 4)
+        return __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf(a));
+    else
+        return __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(a) * (1.0f / K));
+}
+template <int K>
+__device__ __forceinline__ float root_squared(float a, float r)
+{
+    if constexpr (K == 2)
+        return a;
+    else if constexpr (K == 4)
+        return __builtin_amdgcn_sqrtf(a);
+    else
+        return r * r;
+}
+
 // y^1 .. y^K of the signed K-th root of v.
 template <int K>
 __device__ __forceinline__ void powers(float v, float (&T)[K])
 {
     const float a = __builtin_fabsf(v);
-    if constexpr (K == 1) {
-        T[0] = v;
-    } else if constexpr (K == 2) {
-        float r = __builtin_amdgcn_sqrtf(a);
-        T[0] = __builtin_copysignf(r, v);
-        T[1] = a;
-    } else if constexpr (K == 4) {
-        float r2 = __builtin_amdgcn_sqrtf(a);
-        float r = __builtin_amdgcn_sqrtf(r2);
-        T[0] = __builtin_copysignf(r, v);
+    const float r = root<K>(a), r2 = root_squared<K>(a, r);
+    T[0] = __builtin_copysignf(r, v);
+    if constexpr (K > 1)
         T[1] = r2;
+    if constexpr (K > 2)
         T[2] = T[0] * r2;
-        T[3] = a;
-    } else {
-        // |v|^(1/K) = 2^(log2|v| / K); v = 0 gives 2^-inf = 0
-        float r = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(a) * (1.0f / K));
-        float r2 = r * r;
-        T[0] = __builtin_copysignf(r, v);
-        T[1] = r2;
-        T[2] = T[0] * r2;
-        if constexpr (K == 3) {
-            T[2] = v;
-        } else {
-            T[3] = r2 * r2;
-            if constexpr (K == 5) {
-                T[4] = v;
-            } else {
-                T[4] = T[2] * r2;
-                T[5] = a;
-            }
-        }
-    }
-}
-
-// The sums one element feeds: y^1 .. y^K, then -- with coherence-factor
-// weighting -- the sample itself and its square.
-template <int K, bool CF>
-constexpr int n_sums() { return K + (CF ? 2 : 0); }
-
-template <int K, bool CF>
-__device__ __forceinline__ void terms(float v, float (&T)[n_sums<K, CF>()])
-{
-    float Y[K];
-    powers<K>(v, Y);
-#pragma unroll
-    for (int j = 0; j < K; ++j)
-        T[j] = Y[j];
-    if constexpr (CF) {
-        T[K] = v;
-        T[K + 1] = v * v;
-    }
+    if constexpr (K > 3)
+        T[3] = r2 * r2;
+    if constexpr (K > 4)
+        T[4] = T[2] * r2;
+    if constexpr (K > 2)
+        T[K - 1] = K % 2 ? v : a;      // y^K is the sample itself, or its magnitude
 }
 
 // LDS layout of a staged chunk: rows of window + 2 floats.  Rows [0, nch) hold
@@ -397,19 +379,166 @@ __device__ __forceinline__ int xcd_tile(int b, int n)
     return x * q + min(x, r) + l;
 }
 
-// Power-sum accumulation.  Compensated mode: four elements are summed pairwise,
-// eight such groups (32 elements) accumulate in a plain float32 partial, and the
-// partial enters the running sum with one Kahan step.  The rounding error then
-// stays at a few units of the partials' magnitude instead of growing with N.
-template <int K>
-__device__ __forceinline__ void flush(float (&s)[K], float (&c)[K], float (&P)[K])
-{
+// Power-sum accumulation.  Compensated mode: the terms of four elements are
+// summed by themselves (PixelSums::add_group), eight such groups (32 elements)
+// accumulate in a plain float32 partial, and the partial enters the running
+// sum with one Kahan step.  The rounding error then stays at a few units of
+// the partials' magnitude instead of growing with N.
+template <int N, bool COMP>
+struct PowerSums {
+    float s[N], c[N];     // running sums, compensations
+    float P[N];           // the current block's partials
+    __device__ __forceinline__ void clear()
+    {
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        kahan_add(s[j], c[j], P[j]);
-        P[j] = 0.f;
+        for (int j = 0; j < N; ++j) {
+            s[j] = 0.f;
+            c[j] = 0.f;
+        }
+    }
+    // at each chunk's start: the partials need no registers while rows are staged
+    __device__ __forceinline__ void start_block()
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            P[j] = 0.f;
+    }
+    __device__ __forceinline__ void add(int j, float a)
+    {
+        if (COMP)
+            P[j] += a;
+        else
+            s[j] += a;
+    }
+    __device__ __forceinline__ void flush()
+    {
+        if (COMP) {
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                kahan_add(s[j], c[j], P[j]);
+            start_block();
+        }
+    }
+    // the split groups' combination: (sum, compensation) pairs through LDS
+    static constexpr int kFloats = 2 * N;
+    __device__ __forceinline__ void put(float* red) const
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            red[2 * j] = s[j];
+            red[2 * j + 1] = c[j];
+        }
+    }
+    __device__ __forceinline__ void take(const float* red)
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const float so = red[2 * j], co = red[2 * j + 1];
+            if (COMP) {
+                kahan_add(s[j], c[j], so);
+                kahan_add(s[j], c[j], -co);
+            } else {
+                s[j] += so;
+            }
+        }
+    }
+    template <class R>
+    __device__ __forceinline__ R value(int j) const { return COMP ? R(s[j]) - R(c[j]) : R(s[j]); }
+};
+
+// a_0 + .. + a_3, and a_0 b_0 + .. + a_3 b_3 without rounding the products but
+// the first: four instructions, where forming the products first takes seven.
+__device__ __forceinline__ float sum4(const float (&a)[4]) { return (a[0] + a[1]) + (a[2] + a[3]); }
+__device__ __forceinline__ float dot4(const float (&a)[4], const float (&b)[4])
+{
+    return __builtin_fmaf(a[3], b[3], __builtin_fmaf(a[2], b[2], __builtin_fmaf(a[1], b[1], a[0] * b[0])));
+}
+
+// y^1 .. y^K of four elements' signed K-th roots, each power summed over the
+// four.  Bound by VALU issue, so every power that no later power needs is formed
+// inside its sum (dot4): 8.5 instead of 10 instructions per element at K = 6,
+// 6.5 instead of 8 at K = 5, 0.75 fewer at K = 3 and 4.  Measured: int16, 256
+// elements, 1024 x 1024, order 6 231.3 -> 225.3 us; float32 mirror pairs, 128
+// elements, 2048 x 2048, order 5 300.6 -> 289.6 us; the six orders of eight
+// 512 x 512 frames 823 -> 802 us.  (Carrying the symmetric sums themselves,
+// e_m += y e_{m-1}, takes fewer instructions still, but where the array's
+// halves cancel their partial sums exceed the result a thousandfold, and a
+// float32 rounding of one with it.)
+template <int K>
+__device__ __forceinline__ void power_sums4(const float (&v)[4], float (&S)[K])
+{
+    float r[4], y[4], a[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        a[m] = __builtin_fabsf(v[m]);
+        r[m] = root<K>(a[m]);
+        y[m] = __builtin_copysignf(r[m], v[m]);
+    }
+    S[0] = sum4(y);
+    if constexpr (K == 2) {
+        S[1] = sum4(a);
+    } else if constexpr (K == 3) {
+        S[1] = dot4(r, r);
+        S[2] = sum4(v);
+    } else if constexpr (K > 3) {
+        float r2[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            r2[m] = root_squared<K>(a[m], r[m]);
+        S[1] = sum4(r2);
+        S[2] = dot4(y, r2);
+        if constexpr (K == 4) {
+            S[3] = sum4(a);
+        } else if constexpr (K == 5) {
+            S[3] = dot4(r2, r2);
+            S[4] = sum4(v);
+        } else {
+            float r4[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                r4[m] = r2[m] * r2[m];
+            S[3] = sum4(r4);
+            S[4] = dot4(y, r4);
+            S[5] = sum4(a);
+        }
     }
 }
+
+// What one pixel accumulates: its order's power sums and -- with
+// coherence-factor weighting -- the sums of the samples and of their squares.
+template <int K, bool CF, bool COMP>
+struct PixelSums : PowerSums<K + (CF ? 2 : 0), COMP> {
+    __device__ __forceinline__ void add_group(const float (&v)[4])
+    {
+        if constexpr (COMP) {
+            float S[K];
+            power_sums4<K>(v, S);
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                this->add(j, S[j]);
+            if constexpr (CF) {
+                this->add(K, sum4(v));
+                this->add(K + 1, dot4(v, v));
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                add_one(v[m]);
+        }
+    }
+    __device__ __forceinline__ void add_one(float v)
+    {
+        float T[K];
+        powers<K>(v, T);
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            this->add(j, T[j]);
+        if constexpr (CF) {
+            this->add(K, v);
+            this->add(K + 1, v * v);
+        }
+    }
+};
 
 __device__ __forceinline__ void load_group(ConstEntry E, hodmas_chan_entry (&e)[4])
 {
@@ -430,10 +559,10 @@ __device__ __forceinline__ void load_group(ConstEntry E, hodmas_chan_entry (&e)[
 // on entry and the next group's on return; (u2f, qf) are the lane's pixel
 // moved 16 - 3*SH columns to the left; ro / ron: the LDS row offsets of this
 // group's slots and, loaded with the next group's constants, of the next.
-template <int K, bool CF, bool COMP, bool CHECK, bool HALF, int M, int SH, int NS = n_sums<K, CF>()>
+template <class Sums, bool CHECK, bool HALF, int M, int SH>
 __device__ __forceinline__ void process_group(const hodmas_chan_entry (&e)[4], float u2, float q,
-                                              const float* __restrict__ lds, int moff, int zero, float (&s)[M][NS],
-                                              float (&P)[M][NS], bool more, ConstEntry En,
+                                              const float* __restrict__ lds, int moff, int zero, Sums (&acc)[M],
+                                              bool more, ConstEntry En,
                                               hodmas_chan_entry (&en)[4], Shared& sh, float u2f, float qf,
                                               const int (&ro)[4], ConstStage Sn, int slot_n, int stride,
                                               int (&ron)[4])
@@ -487,23 +616,8 @@ __device__ __forceinline__ void process_group(const hodmas_chan_entry (&e)[4], f
             load_rowoff(Sn, slot_n, stride, ron);
     }
 #pragma unroll
-    for (int mm = 0; mm < M; ++mm) {
-        float T[4][NS];
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-            terms<K, CF>(v[mm][m], T[m]);
-#pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            if (COMP) {
-                P[mm][j] += (T[0][j] + T[1][j]) + (T[2][j] + T[3][j]);
-            } else {
-                s[mm][j] += T[0][j];
-                s[mm][j] += T[1][j];
-                s[mm][j] += T[2][j];
-                s[mm][j] += T[3][j];
-            }
-        }
-    }
+    for (int mm = 0; mm < M; ++mm)
+        acc[mm].add_group(v[mm]);
     if constexpr (SH > 0) {
         if (more) {
             // the next group's F -- its last element at the moved pixel --
@@ -523,33 +637,22 @@ __device__ __forceinline__ void process_group(const hodmas_chan_entry (&e)[4], f
     }
 }
 
-template <int NS, bool COMP, int M>
-__device__ __forceinline__ void after_group(int& groups, float (&s)[M][NS], float (&c)[M][NS],
-                                            float (&P)[M][NS])
-{
-    if (COMP && (++groups & 7) == 0) {
-#pragma unroll
-        for (int mm = 0; mm < M; ++mm)
-            flush<NS>(s[mm], c[mm], P[mm]);
-    }
-}
-
 // The n elements of this wave's split group in one staged chunk (their
 // constants stored contiguously), four at a time; two constant sets alternate
 // so nothing is copied between them.
-template <int K, bool CF, bool COMP, bool CHECK, bool HALF, int M, int SH, int NS = n_sums<K, CF>()>
+template <class Sums, bool CHECK, bool HALF, int M, int SH>
 __device__ __forceinline__ void accumulate_chunk(ConstEntry E, int n, float u2, float q,
-                                                 const float* __restrict__ lds, int moff, int zero, float (&s)[M][NS],
-                                                 float (&c)[M][NS], ConstStage St, int stride, float u2f, float qf,
-                                                 XF* shbuf)
+                                                 const float* __restrict__ lds, int moff, int zero, Sums (&acc)[M],
+                                                 ConstStage St, int stride, float u2f, float qf, XF* shbuf)
 {
-    float P[M][NS];
+    auto flush = [&]() {
 #pragma unroll
-    for (int mm = 0; mm < M; ++mm) {
+        for (int mm = 0; mm < M; ++mm)
+            acc[mm].flush();
+    };
 #pragma unroll
-        for (int j = 0; j < NS; ++j)
-            P[mm][j] = 0.f;
-    }
+    for (int mm = 0; mm < M; ++mm)
+        acc[mm].start_block();
     int sl = 0;
     if (n >= 4) {
         hodmas_chan_entry ea[4], eb[4];
@@ -573,16 +676,18 @@ __device__ __forceinline__ void accumulate_chunk(ConstEntry E, int n, float u2, 
         int groups = 0;
         while (true) {
             const bool more_a = sl + 8 <= n;
-            process_group<K, CF, COMP, CHECK, HALF, M, SH>(ea, u2, q, lds, moff, zero, s, P, more_a, E + sl + 4, eb,
-                                                           sh, u2f, qf, ra, St, sl + 4, stride, rb);
-            after_group<NS, COMP, M>(groups, s, c, P);
+            process_group<Sums, CHECK, HALF, M, SH>(ea, u2, q, lds, moff, zero, acc, more_a, E + sl + 4, eb, sh, u2f,
+                                                    qf, ra, St, sl + 4, stride, rb);
+            if ((++groups & 7) == 0)
+                flush();
             sl += 4;
             if (!more_a)
                 break;
             const bool more_b = sl + 8 <= n;
-            process_group<K, CF, COMP, CHECK, HALF, M, SH>(eb, u2, q, lds, moff, zero, s, P, more_b, E + sl + 4, ea,
-                                                           sh, u2f, qf, rb, St, sl + 4, stride, ra);
-            after_group<NS, COMP, M>(groups, s, c, P);
+            process_group<Sums, CHECK, HALF, M, SH>(eb, u2, q, lds, moff, zero, acc, more_b, E + sl + 4, ea, sh, u2f,
+                                                    qf, rb, St, sl + 4, stride, ra);
+            if ((++groups & 7) == 0)
+                flush();
             sl += 4;
             if (!more_b)
                 break;
@@ -595,23 +700,12 @@ __device__ __forceinline__ void accumulate_chunk(ConstEntry E, int n, float u2, 
             redirect(tp, e, zero);
 #pragma unroll
         for (int mm = 0; mm < M; ++mm) {
-            float T[NS];
             const int addr = tp.addr + mm * moff;
-            terms<K, CF>(interp<HALF>(tp, lds_at(lds, addr), lds_at(lds, addr + 4)), T);
-#pragma unroll
-            for (int j = 0; j < NS; ++j) {
-                if (COMP)
-                    P[mm][j] += T[j];
-                else
-                    s[mm][j] += T[j];
-            }
+            acc[mm].add_one(interp<HALF>(tp, lds_at(lds, addr), lds_at(lds, addr + 4)));
         }
     }
-    if (COMP) {
-#pragma unroll
-        for (int mm = 0; mm < M; ++mm)
-            flush<NS>(s[mm], c[mm], P[mm]);
-    }
+    if (n & 31)           // else the last group has ended a block
+        flush();
 }
 
 // Newton's identities: e_m = (1/m) sum_{j=1..m} (-1)^(j-1) e_{m-j} p_j.
@@ -645,7 +739,7 @@ template <int K, int DT, bool COMP, bool CF, int M, bool CHECK, int SH = 0>
 __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_tile_desc& td,
                                              float* __restrict__ lds)
 {
-    constexpr int NS = n_sums<K, CF>();
+    using Sums = PixelSums<K, CF, COMP>;
     // rows copied straight into LDS (FP32, FP16) unless the tile is range-tested
     constexpr bool kDirect = !CHECK && (DT == HODMAS_F32 || DT == HODMAS_F16);
     constexpr bool kHalf = kDirect && DT == HODMAS_F16;
@@ -694,15 +788,10 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
         shbuf = reinterpret_cast<XF*>(reinterpret_cast<char*>(lds) + A.shift_off) + (pl >> 4) * kRowEntries + lx;
     }
 
-    float s[M][NS], c[M][NS];
+    Sums acc[M];
 #pragma unroll
-    for (int mm = 0; mm < M; ++mm) {
-#pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            s[mm][j] = 0.f;
-            c[mm][j] = 0.f;
-        }
-    }
+    for (int mm = 0; mm < M; ++mm)
+        acc[mm].clear();
     ConstEntry E = A.entries + td.first_entry;
     ConstStage St = A.stage + td.first_entry;
     for (int c0 = 0; c0 < td.n_active; c0 += A.chunk) {
@@ -720,44 +809,28 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
         for (int h = 0; h < g; ++h)
             goff += (nch - h + A.split - 1) / A.split;
         const int ng = nch > g ? (nch - g + A.split - 1) / A.split : 0;
-        accumulate_chunk<K, CF, COMP, CHECK, kHalf, M, SH>(E + c0 + goff, ng, u2, q, lds, moff, zero, s, c, St + c0,
-                                                            row_stride(td.window), u2f, qf, shbuf);
+        accumulate_chunk<Sums, CHECK, kHalf, M, SH>(E + c0 + goff, ng, u2, q, lds, moff, zero, acc, St + c0,
+                                                    row_stride(td.window), u2f, qf, shbuf);
     }
 
     if (A.split > 1) {
         // fixed-order combination of the groups' partial sums through LDS
-        // floats per pixel and group: (sum, compensation) pairs, padded to an
-        // odd stride so consecutive lanes fall in different LDS banks
-        constexpr int W = 2 * M * NS + 1;
+        // floats per pixel and group: two per sum, padded to an odd stride so
+        // consecutive lanes fall in different LDS banks
+        constexpr int W = M * Sums::kFloats + 1;
         __syncthreads();
         float* red = lds;
         if (g > 0) {
 #pragma unroll
-            for (int mm = 0; mm < M; ++mm) {
-#pragma unroll
-                for (int j = 0; j < NS; ++j) {
-                    red[((g - 1) * npix + pl) * W + 2 * (mm * NS + j)] = s[mm][j];
-                    red[((g - 1) * npix + pl) * W + 2 * (mm * NS + j) + 1] = c[mm][j];
-                }
-            }
+            for (int mm = 0; mm < M; ++mm)
+                acc[mm].put(red + ((g - 1) * npix + pl) * W + mm * Sums::kFloats);
         }
         __syncthreads();
         if (g == 0) {
             for (int gg = 1; gg < A.split; ++gg) {
 #pragma unroll
-                for (int mm = 0; mm < M; ++mm) {
-#pragma unroll
-                    for (int j = 0; j < NS; ++j) {
-                        const float so = red[((gg - 1) * npix + pl) * W + 2 * (mm * NS + j)];
-                        const float co = red[((gg - 1) * npix + pl) * W + 2 * (mm * NS + j) + 1];
-                        if (COMP) {
-                            kahan_add(s[mm][j], c[mm][j], so);
-                            kahan_add(s[mm][j], c[mm][j], -co);
-                        } else {
-                            s[mm][j] += so;
-                        }
-                    }
-                }
+                for (int mm = 0; mm < M; ++mm)
+                    acc[mm].take(red + ((gg - 1) * npix + pl) * W + mm * Sums::kFloats);
             }
         }
     }
@@ -769,12 +842,12 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
         R p[K];
 #pragma unroll
         for (int j = 0; j < K; ++j)
-            p[j] = COMP ? R(s[mm][j]) - R(c[mm][j]) : R(s[mm][j]);
+            p[j] = acc[mm].template value<R>(j);
         const R ek = newton<K, R>(p);
         if constexpr (CF) {
             // coherence factor (sum v)^2 / (N sum v^2) of the normalised samples
-            const double s1 = COMP ? double(s[mm][K]) - double(c[mm][K]) : double(s[mm][K]);
-            const double s2 = COMP ? double(s[mm][K + 1]) - double(c[mm][K + 1]) : double(s[mm][K + 1]);
+            const double s1 = acc[mm].template value<double>(K);
+            const double s2 = acc[mm].template value<double>(K + 1);
             const double cf = s2 > 0.0 ? (s1 * s1) / (double(A.n_elements) * s2) : 0.0;
             *dst(mm) = (float)(double(ek) * cf * double(A.out_scale));
         } else {

@@ -146,6 +146,24 @@ def test_small_ragged_frames(hd, tiling, dtype):
     plan.close()
 
 
+@pytest.mark.parametrize("tiling", [(16, 16, 1, 67), (16, 16, 1, 33), (8, 8, 4, 67)])
+@pytest.mark.parametrize("n", [6, 31, 32, 33, 64, 67])
+def test_orders_across_blocks_of_elements(hd, n, tiling):
+    """Element counts on either side of the groups of 4 and blocks of 32 the
+    sums accumulate in, whole and left over at a chunk's end, with and without
+    split groups, every pixel within its error bound."""
+    f = ph.make_frame(n, 600, 40, 30, n_points=8, snr_db=15.0, seed=23 + n)
+    grid = ph.make_grid(40, 30, 4e-3, 9e-3)
+    arr = ph.to_fp32(f.rf)
+    plan = hd.Plan(f.geometry, grid, 600, "f32", max_order=6, tiling=tiling)
+    bounds = EB.pixel_bounds(arr, f.geometry, grid, range(3, 7), plan_eps(plan, f.geometry, grid))
+    for k in range(3, 7):
+        say("blocks n=%d tiling %s order %d" % (n, tiling, k))
+        g = gpu_image(hd, plan, arr, k)
+        check_pixels(g, oracle_image(arr, 1.0, f.geometry, grid, k), bounds, k, "blocks n=%d %s k=%d" % (n, tiling, k))
+    plan.close()
+
+
 def test_single_element_and_order_above_n(hd):
     f = ph.make_frame(1, 256, 9, 11, n_points=2, seed=4)
     grid = ph.make_grid(9, 11, 3e-3, 5e-3)
