@@ -142,3 +142,57 @@ def test_display_batch_equals_single_runs(hd):
     with pytest.raises(ValueError):
         disp.run_batch([])
     disp.close()
+
+
+@pytest.mark.parametrize("nz", [2, 4, 8, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096, 8192])
+def test_every_length_column_by_column(hd, nz):
+    """Every transform length (each has its own stages), an odd number of
+    columns, filters that reach past both ends; neighbouring columns of very
+    different brightness, each held to the tolerance by itself, since two of
+    them share a transform.  Alone and as part of a batch (other groups of
+    columns per workgroup)."""
+    nx, dz = 35, 0.075e-3
+    rng = np.random.default_rng(nz)
+    img = (rng.standard_normal((nz, nx)) * 10.0 ** rng.integers(-12, 13, nx)).astype(np.float32)
+    img[:, 7] = 0.0
+    for numtaps in (1, 7, 255):
+        say("columns nz=%d taps %d" % (nz, numtaps))
+        disp = hd.Display(nx, nz, dz, 1540.0, 2e6, 8e6, numtaps, 60.0)
+        dev = torch.from_numpy(img).cuda()
+        env = torch.empty_like(dev)
+        disp.run(dev, env)
+        many = [torch.empty_like(dev) for _ in range(16)]
+        disp.run_batch([dev] * 16, many)
+        torch.cuda.synchronize()
+        assert torch.equal(env, many[15])
+        g = env.cpu().numpy().astype(np.float64)
+        _, o, _ = D.display(img.astype(np.float64), dz, 1540.0, 2e6, 8e6, numtaps, 60.0)
+        assert np.all(g[:, 7] == 0.0)
+        n = np.linalg.norm(o, axis=0)
+        err = np.linalg.norm(g - o, axis=0)[n > 0] / n[n > 0]
+        say("nz=%d taps %d: worst column rel L2 %.2e" % (nz, numtaps, err.max()))
+        assert err.max() <= TOL_ENV
+        disp.close()
+
+
+@pytest.mark.parametrize("nz", [64, 1024])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_column_that_is_not_finite_stays_alone(hd, nz, bad):
+    nx, dz = 10, 0.075e-3
+    rng = np.random.default_rng(3)
+    img = torch.from_numpy(rng.standard_normal((nz, nx)).astype(np.float32)).cuda()
+    disp = hd.Display(nx, nz, dz, 1540.0, 2e6, 8e6, 31, 60.0)
+    whole, hurt = torch.empty_like(img), torch.empty_like(img)
+    disp.run(img, whole)
+    img2 = img.clone()
+    img2[nz // 2, 4] = bad
+    disp.run(img2, hurt)
+    torch.cuda.synchronize()
+    keep = [c for c in range(nx) if c not in (4, 5)]
+    assert torch.equal(whole[:, keep], hurt[:, keep])
+    assert bool(torch.isnan(hurt[:, 4]).all())
+    # the column that shares its transform: other roundings, the same envelope
+    _, o, _ = D.display(img.cpu().numpy().astype(np.float64), dz, 1540.0, 2e6, 8e6, 31, 60.0)
+    g = hurt[:, 5].cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(g - o[:, 5]) <= TOL_ENV * np.linalg.norm(o[:, 5])
+    disp.close()
