@@ -447,9 +447,12 @@ typedef struct {
     double mu_in, mu_out, sigma_out;
 } hodmas_metrics;
 
-/* image_dev: device float32 [nz][nx].  Runs one workgroup on `stream`, waits
- * for it and fills *out (host).  Allocates and frees a few bytes of device
- * memory: an evaluation call, not for the hot path.  Errors: EINVAL (null
+/* image_dev: device float32 [nz][nx].  Runs three launches on `stream`, waits
+ * for them and fills *out (host): an evaluation call, not for the hot path.
+ * Works in fixed device memory of the library (352 KiB per GPU, eight
+ * workspaces, each taken for the length of one call; the first call on a GPU
+ * allocates eight results of pinned host memory, held until the process ends);
+ * a ninth concurrent call allocates and frees its own.  Errors: EINVAL (null
  * pointers, empty or out-of-image rectangles, dx_m <= 0, bins outside
  * 2..4096), ENOMEM, EDEVICE. */
 hodmas_status hodmas_image_metrics(const float* image_dev, int32_t nx, int32_t nz, double dx_m,

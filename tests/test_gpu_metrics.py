@@ -75,3 +75,47 @@ def test_higher_orders_raise_contrast_and_narrow_targets(hd):
     assert res[5]["fwhm_m"] < res[1]["fwhm_m"]
     disp.close()
     plan.close()
+
+
+@pytest.mark.parametrize("nz,nx,t,b", [
+    (9, 7, (3, 4, 5, 6), (0, 7, 0, 9)),                        # one pixel
+    (70, 64, (0, 64, 0, 64), (0, 64, 6, 70)),                  # one workgroup's pixels exactly
+    (80, 65, (0, 64, 0, 65), (0, 65, 0, 80)),                  # ... and a few more
+    (900, 1100, (300, 1063, 10, 700), (0, 1100, 0, 900)),      # more than the most workgroups' share
+])
+def test_regions_of_any_size_match_oracle(hd, nz, nx, t, b):
+    rng = np.random.default_rng(nz)
+    img = rng.rayleigh(0.3, (nz, nx)).astype(np.float32)
+    cx, cz = (t[0] + t[1]) / 2 - 0.3, (t[2] + t[3]) / 2
+    zz, xx = np.mgrid[0:nz, 0:nx]
+    img += (3.0 * np.exp(-0.5 * (((xx - cx) / 9.5) ** 2 + ((zz - cz) / 6.0) ** 2))).astype(np.float32)
+    img[t[2]:t[3], t[0]:t[1]].flat[-1] = img[t[2]:t[3], t[0]:t[1]].max()     # a second maximum, later
+    got = hd.image_metrics(torch.from_numpy(img).cuda(), 0.1e-3, t, b, 100)
+    for k, v in oracle_metrics(img.astype(np.float64), 0.1e-3, t, b, 100).items():
+        assert got[k] == pytest.approx(v, rel=1e-9, abs=1e-12), k
+
+
+def test_evaluations_from_many_threads(hd):
+    """More host threads than the library keeps workspaces for, each with its
+    own image and stream, evaluate at once: every result is its own image's."""
+    import threading
+    rng = np.random.default_rng(11)
+    n = 14
+    imgs = [torch.from_numpy((rng.rayleigh(1.0 + i, (200, 300))).astype(np.float32)).cuda() for i in range(n)]
+    t, b = (20, 90, 30, 120), (100, 300, 0, 200)
+    alone = [hd.image_metrics(im, 1e-4, t, b) for im in imgs]
+    torch.cuda.synchronize()
+    got, start = [None] * n, threading.Barrier(n)
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        start.wait()
+        got[i] = [hd.image_metrics(imgs[i], 1e-4, t, b, stream=stream) for _ in range(20)]
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(n)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    for i in range(n):
+        assert all(g == alone[i] for g in got[i]), i
