@@ -185,11 +185,10 @@ hodmas_status build_tables(hodmas_plan_s* p)
     } catch (const std::bad_alloc&) {
         return HODMAS_ENOMEM;
     }
-    // FP32 / FP16 rows are copied straight into LDS through one buffer
+    // untested tiles' rows are copied straight into LDS through one buffer
     // resource over the frame, whose range is a 32-bit byte count
     const int64_t esz = p->rf.dtype == HODMAS_F32 ? 4 : 2;
-    const bool copies = p->rf.dtype == HODMAS_I16 ||
-                        int64_t(n) * p->rf.channel_stride * esz < (int64_t(1) << 31);
+    const bool copies = int64_t(n) * p->rf.channel_stride * esz < (int64_t(1) << 31);
     const int chunk = p->tiling.chunk;
     const int split = p->tiling.split;
     int32_t max_window = 2;
@@ -238,8 +237,8 @@ hodmas_status build_tables(hodmas_plan_s* p)
             }
             // every staged row -- `window` samples from the element's first --
             // must lie inside the record for the untested path, which copies
-            // FP32 and FP16 rows without bounds and tests no delay; so must
-            // the whole record inside one 32-bit buffer range
+            // rows without bounds and tests no delay; so must the whole frame
+            // inside one 32-bit buffer range
             for (int i = 0; i < n && !check; ++i)
                 check = act[i] && (wlo[i] < 0 || int64_t(wlo[i]) + window > S);
             check = check || !copies;

@@ -65,11 +65,6 @@ __device__ __forceinline__ Global<T> global_ptr(T* p)
     return (Global<T>)p;
 }
 
-template <int DT> struct Storage;
-template <> struct Storage<HODMAS_F32> { using T = float; };
-template <> struct Storage<HODMAS_F16> { using T = _Float16; };
-template <> struct Storage<HODMAS_I16> { using T = short; };
-
 // Word 3 of a raw (stride 0) buffer resource on gfx950: 32-bit data format,
 // no swizzle; with stride 0 an access is in range iff its byte offset is below
 // the resource's size.
@@ -252,120 +247,143 @@ __device__ __forceinline__ int row_stride(int window) { return window + 2; }
 __device__ __forceinline__ int zero_offset(int window) { return window * 4; }
 __device__ __forceinline__ int mirror_offset(int nch, int window) { return nch * row_stride(window) * 4; }
 
-template <int DT, int M>
-__device__ __forceinline__ void stage_chunk(const FrameArgs& A, ConstStage st, int nch, int window,
-                                            float* __restrict__ lds, int wave, int nwaves, int lane)
+// The rows a wave stages are a contiguous run of the chunk's; lane j holds the
+// table entry of the run's row c + j.  One vector load brings 64 rows'
+// entries; those of the first 64 are requested a chunk ahead, with the rows of
+// the chunk before, so that a chunk's staging starts with its rows' loads.
+// A row inside the record needs the byte offset in the frame of LDS window
+// position 0, in `at`; others (CHECK) its index in the record, and the record.
+struct Rows {
+    int at, channel;
+};
+
+struct RowRun {
+    int s0, s1;               // the wave's rows
+};
+template <int M>
+__device__ __forceinline__ RowRun row_run(int nch, int wave, int nwaves)
 {
-    using T = typename Storage<DT>::T;
-    constexpr int esz = int(sizeof(T));
-    // Each wave stages a contiguous run of rows; lanes run along the window.
-    // Latency, not bandwidth, sets the cost here: one vector load brings 64
-    // rows' table entries (lane j holds row j), then the sample loads go out
-    // kInFlight at a time before any wait.  Each row is read through a buffer
-    // resource spanning exactly its channel's record, built in scalar
-    // registers from the entry lanes: a sample index outside [0, S) -- before
-    // the record, past its end, or negative -- is out of the resource's range
-    // and loads as zero in hardware, so no lane clamps or selects.
-    constexpr int kInFlight = 16;
     const int rows = M * nch;
     const int per_wave = (rows + nwaves - 1) / nwaves;
     const int s0 = wave * per_wave;
-    const int s1 = min(rows, s0 + per_wave);
+    return {s0, min(rows, s0 + per_wave)};
+}
+
+template <int DT, int M, bool CHECK>
+__device__ __forceinline__ Rows load_rows(const FrameArgs& A, ConstStage st, int nch, RowRun run, int c, int lane)
+{
     const Global<const int> ent = global_ptr(reinterpret_cast<const int*>(st));
-    const char* rf = static_cast<const char*>(A.rf);
-    const int64_t row_bytes = int64_t(A.stride) * esz;
-    const int record_bytes = A.n_samples * esz;
+    const int j = max(min(c + lane, run.s1 - 1), 0);
+    const bool mirrored = M == 2 && j >= nch;
+    const int src = mirrored ? j - nch : j;
+    const int elem = ent[2 * src];
+    const int channel = mirrored ? A.n_elements - 1 - elem : elem, first = ent[2 * src + 1];
+    if constexpr (!CHECK)
+        return {(channel * (int)A.stride + first) * (DT == HODMAS_F32 ? 4 : 2), 0};
+    else
+        return {first, channel};
+}
+
+// Rows are copied from memory straight into LDS: buffer loads that write LDS,
+// one per 64 samples, so a row costs a lane read or two, scalar work and one
+// load per wave -- no vector registers in flight and one wait for all of them.
+// A 2-byte sample lands, zero-extended, in the low half of its LDS word (the
+// layout of FP32 rows); FP16 is widened by the interpolation, int16 codes by a
+// pass of each wave over its own rows (widen_codes).
+// Rows inside the record (CHECK false) are read through one buffer resource
+// over the whole frame, the row's start in the scalar offset.  Rows of tiles
+// that reach the record ends are read through a resource of their own record,
+// each lane's sample index clamped into it: a delay inside the record meets a
+// clamped sample only as the neighbour of the record's last one, with weight
+// zero, and every other delay is pointed at the zero pair (redirect).
+template <int DT, int M, bool CHECK>
+__device__ __forceinline__ void stage_direct(const FrameArgs& A, ConstStage st, Rows r, int nch, RowRun run,
+                                             int window, float* __restrict__ lds, int lane)
+{
+    constexpr int esz = DT == HODMAS_F32 ? 4 : 2;
+    using LdsPtr = __attribute__((address_space(3))) void*;
     const int stride = row_stride(window);
-    if (wave == 0 && lane < 2 * M)
-        lds[(lane >> 1) * nch * stride + window + (lane & 1)] = 0.f;
-    for (int c = s0; c < s1; c += 64) {
-        const int j = min(c + lane, s1 - 1);
-        const bool mirrored = M == 2 && j >= nch;
-        const int src = mirrored ? j - nch : j;
-        const int elem = ent[2 * src];
-        const int my_channel = mirrored ? A.n_elements - 1 - elem : elem;
-        const int my_first = ent[2 * src + 1];
-        const int cend = min(s1 - c, 64);
-        for (int base = 0; base < window; base += 64) {
-            const int i = base + lane;
-            for (int m0 = 0; m0 < cend; m0 += kInFlight) {
-                float v[kInFlight];
-#pragma unroll
-                for (int m = 0; m < kInFlight; ++m) {
-                    const int ch = __builtin_amdgcn_readlane(my_channel, m0 + m);
-                    const int first = __builtin_amdgcn_readlane(my_first, m0 + m);
-                    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                        const_cast<char*>(rf + ch * row_bytes), (short)0, record_bytes, kBufferFlags);
-                    const int off = (first + i) * esz;
-                    if constexpr (DT == HODMAS_F32)
-                        v[m] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
-                    else if constexpr (DT == HODMAS_F16)
-                        v[m] = (float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0));
-                    else
-                        v[m] = (float)(short)__builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
+    auto copy = [&](__amdgpu_buffer_rsrc_t rs, int row, int b, int voff, int soff) {
+        // the builtin takes the size as a constant
+        if constexpr (DT == HODMAS_F32)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LdsPtr)(lds + row * stride + b), 4, voff, soff, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LdsPtr)(lds + row * stride + b), 2, voff, soff, 0, 0);
+    };
+    for (int c = run.s0; c < run.s1; c += 64) {
+        if (c > run.s0)
+            r = load_rows<DT, M, CHECK>(A, st, nch, run, c, lane);
+        const int cend = __builtin_amdgcn_readfirstlane(min(run.s1 - c, 64));
+        if constexpr (CHECK) {
+            const char* rf = static_cast<const char*>(A.rf);
+            const int64_t row_bytes = int64_t(A.stride) * esz;
+            for (int b = 0; b < window; b += 64) {
+                if (b + lane < window) {
+                    for (int m = 0; m < cend; ++m) {
+                        const int ch = __builtin_amdgcn_readlane(r.channel, m);
+                        const int first = __builtin_amdgcn_readlane(r.at, m);
+                        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                            const_cast<char*>(rf + ch * row_bytes), (short)0, A.n_samples * esz, kBufferFlags);
+                        copy(rs, c + m, b, max(0, min(first + b + lane, A.n_samples - 1)) * esz, 0);
+                    }
                 }
-#pragma unroll
-                for (int m = 0; m < kInFlight; ++m) {
-                    const int row = c + m0 + m;
-                    if (m0 + m < cend && i < window)
-                        lds[row * stride + i] = v[m] * A.in_scale;
+            }
+        } else {
+            const int bytes = A.n_elements * (int)A.stride * esz;   // below 2^31: the plan tests every tile otherwise
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(A.rf), (short)0, bytes, kBufferFlags);
+            for (int b = 0; b < window; b += 64) {
+                if (b + lane < window) {
+                    for (int m = 0; m < cend; ++m)
+                        copy(rs, c + m, b, (b + lane) * esz, __builtin_amdgcn_readlane(r.at, m));
                 }
             }
         }
     }
 }
 
-// FP32 and FP16 tiles whose rows lie inside the record (the plan marks the
-// others as tested) copy each row from memory straight into LDS: buffer loads
-// that write LDS, one per 64 samples, through one buffer resource over the
-// whole frame, with the row's start in the scalar offset.  One vector pass
-// forms 64 rows' offsets (lane j: row j), so a row then costs one lane read,
-// scalar work and one load per wave -- no vector registers in flight, no
-// conversion and no LDS store, where the general staging above spends several
-// vector instructions per row.  An FP16 sample lands, zero-extended, in the
-// low half of its LDS word (the layout of FP32 rows); the interpolation
-// widens it.
-template <int DT, int M>
-__device__ __forceinline__ void stage_direct(const FrameArgs& A, ConstStage st, int nch, int window,
-                                             float* __restrict__ lds, int wave, int nwaves, int lane)
+// int16 codes in a wave's own rows dequantised and scaled in place, the pads
+// between rows with them (the zero pair stays zero); eight times 64 words at a
+// time, so the reads of one wave overlap.
+__device__ __forceinline__ void widen_codes(float* __restrict__ lds, int begin, int end, float scale, int lane)
 {
-    static_assert(DT == HODMAS_F32 || DT == HODMAS_F16, "direct copies move 4- or 2-byte samples");
-    constexpr int esz = DT == HODMAS_F32 ? 4 : 2;
-    using LdsPtr = __attribute__((address_space(3))) void*;
-    const int rows = M * nch;
-    const int per_wave = (rows + nwaves - 1) / nwaves;
-    const int s0 = wave * per_wave;
-    const int s1 = min(rows, s0 + per_wave);
+    constexpr int kAhead = 8;
+    for (int b = begin; b < end; b += 64 * kAhead) {
+        int w[kAhead];
+#pragma unroll
+        for (int m = 0; m < kAhead; ++m)
+            w[m] = __builtin_bit_cast(int, lds[min(b + m * 64 + lane, end - 1)]);
+#pragma unroll
+        for (int m = 0; m < kAhead; ++m)
+            if (b + m * 64 + lane < end)
+                lds[b + m * 64 + lane] = (float)(short)w[m] * scale;
+    }
+}
+
+// One chunk's rows into LDS; `r` holds the wave's first rows on entry and
+// those of the next chunk (from st + nch, `next` slots of it) on return.
+template <int DT, int M, bool CHECK>
+__device__ __forceinline__ void stage_chunk(const FrameArgs& A, ConstStage st, Rows& r, int nch, int next, int window,
+                                            float* __restrict__ lds, int wave, int nwaves, int lane)
+{
+    const RowRun run = row_run<M>(nch, wave, nwaves);
     const int stride = row_stride(window);
-    if (wave == 0 && lane < 2 * M)
-        lds[(lane >> 1) * nch * stride + window + (lane & 1)] = 0.f;
-    const int bytes = A.n_elements * (int)A.stride * esz;   // below 2^31: the plan tests every tile otherwise
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(A.rf), (short)0, bytes, kBufferFlags);
-    const Global<const int> ent = global_ptr(reinterpret_cast<const int*>(st));
-    for (int c = s0; c < s1; c += 64) {
-        const int j = min(c + lane, s1 - 1);
-        const bool mirrored = M == 2 && j >= nch;
-        const int src = mirrored ? j - nch : j;
-        const int elem = ent[2 * src];
-        const int ch = mirrored ? A.n_elements - 1 - elem : elem;
-        const int my_off = (ch * (int)A.stride + ent[2 * src + 1]) * esz;
-        const int cend = __builtin_amdgcn_readfirstlane(min(s1 - c, 64));
-        for (int b = 0; b < window; b += 64) {
-            if (b + lane < window) {
-                for (int m = 0; m < cend; ++m) {
-                    const int soff = __builtin_amdgcn_readlane(my_off, m);
-                    if constexpr (DT == HODMAS_F32)
-                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LdsPtr)(lds + (c + m) * stride + b), 4,
-                                                                 (b + lane) * 4, soff, 0, 0);
-                    else
-                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LdsPtr)(lds + (c + m) * stride + b), 2,
-                                                                 (b + lane) * 2, soff, 0, 0);
-                }
-            }
-        }
+    // the zero pairs, each by the wave whose row it follows (widen_codes runs
+    // over the wave's rows and pads)
+#pragma unroll
+    for (int mm = 0; mm < M; ++mm) {
+        const int row = mm * nch;
+        if (row >= run.s0 && row < run.s1 && lane < 2)
+            lds[row * stride + window + lane] = 0.f;
+    }
+    stage_direct<DT, M, CHECK>(A, st, r, nch, run, window, lds, lane);
+    if (next > 0) {
+        const RowRun after = row_run<M>(next, wave, nwaves);
+        r = load_rows<DT, M, CHECK>(A, st + nch, next, after, after.s0, lane);
     }
     __builtin_amdgcn_s_waitcnt(0);   // the copies are in LDS before the caller's barrier
+    if constexpr (DT == HODMAS_I16)
+        widen_codes(lds, run.s0 * stride, run.s1 * stride, A.in_scale, lane);
 }
 
 // Workgroups are dealt to the eight XCDs round-robin (workgroup b runs on XCD
@@ -740,9 +758,7 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
                                              float* __restrict__ lds)
 {
     using Sums = PixelSums<K, CF, COMP>;
-    // rows copied straight into LDS (FP32, FP16) unless the tile is range-tested
-    constexpr bool kDirect = !CHECK && (DT == HODMAS_F32 || DT == HODMAS_F16);
-    constexpr bool kHalf = kDirect && DT == HODMAS_F16;
+    constexpr bool kHalf = DT == HODMAS_F16;
     const int tid = threadIdx.x;
     const int npix = A.block / A.split;
     const int nwaves = A.block >> 6;
@@ -794,13 +810,14 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
         acc[mm].clear();
     ConstEntry E = A.entries + td.first_entry;
     ConstStage St = A.stage + td.first_entry;
+    const int nch0 = min(A.chunk, td.n_active);
+    const RowRun run0 = row_run<M>(nch0, wave, nwaves);
+    Rows rows = load_rows<DT, M, CHECK>(A, St, nch0, run0, run0.s0, lane);
     for (int c0 = 0; c0 < td.n_active; c0 += A.chunk) {
         const int nch = min(A.chunk, td.n_active - c0);
         __syncthreads();                       // previous readers of the LDS are done
-        if constexpr (kDirect)
-            stage_direct<DT, M>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
-        else
-            stage_chunk<DT, M>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
+        stage_chunk<DT, M, CHECK>(A, St + c0, rows, nch, min(A.chunk, td.n_active - c0 - nch), td.window, lds, wave,
+                                  nwaves, lane);
         __syncthreads();
         const int moff = mirror_offset(nch, td.window);  // bytes from a slot's row to its mirrored row
         const int zero = zero_offset(td.window);
@@ -1145,8 +1162,7 @@ __device__ __forceinline__ void orders_tile(const FrameArgs& A, const OrderImage
                                             float* __restrict__ lds)
 {
     constexpr int NT = kSums;
-    constexpr bool kDirect = !CHECK && (DT == HODMAS_F32 || DT == HODMAS_F16);
-    constexpr bool kHalf = kDirect && DT == HODMAS_F16;
+    constexpr bool kHalf = DT == HODMAS_F16;
     const int tid = threadIdx.x;
     const int npix = A.block / A.split;
     const int nwaves = A.block >> 6;
@@ -1174,13 +1190,16 @@ __device__ __forceinline__ void orders_tile(const FrameArgs& A, const OrderImage
     }
     ConstEntry E = A.entries + td.first_entry;
     ConstStage St = A.stage + td.first_entry;
+    const int nch0 = min(A.chunk, td.n_active);
+    const RowRun run0 = row_run<1>(nch0, wave, nwaves);
+    Rows rows{0, 0};
+    if (nch0 > 0)
+        rows = load_rows<DT, 1, CHECK>(A, St, nch0, run0, run0.s0, lane);
     for (int c0 = 0; c0 < td.n_active; c0 += A.chunk) {
         const int nch = min(A.chunk, td.n_active - c0);
         __syncthreads();
-        if constexpr (kDirect)
-            stage_direct<DT, 1>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
-        else
-            stage_chunk<DT, 1>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
+        stage_chunk<DT, 1, CHECK>(A, St + c0, rows, nch, min(A.chunk, td.n_active - c0 - nch), td.window, lds, wave,
+                                  nwaves, lane);
         __syncthreads();
         int goff = 0;
         for (int h = 0; h < g; ++h)
