@@ -164,6 +164,33 @@ def test_orders_across_blocks_of_elements(hd, n, tiling):
     plan.close()
 
 
+@pytest.mark.parametrize("mirror", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "i16"])
+def test_waves_that_stage_more_than_64_rows(hd, dtype, mirror):
+    """A chunk of 272 rows (68 per wave: more than one vector of table entries),
+    a second, ragged chunk, with rows inside the record and, with the record
+    test forced, through the clamped copies; the record's own ends as well (the
+    grid's last rows lie past them)."""
+    n, S, nx, nz = 280, 500, 64, 48
+    f = ph.make_frame(n, S, 8, 8, n_points=12, snr_db=15.0, seed=41, pitch=0.04e-3)
+    grid = ph.Grid(nx=nx, nz=nz, x0_m=-(nx - 1) * 0.02e-3, dx_m=0.04e-3, z0_m=16.5e-3, dz_m=0.05e-3)
+    arr, scale = stored(f.rf, dtype, seed=41)
+    fl = hd.FLAG_MIRROR if mirror else 0
+    chunk = 136 if mirror else 272
+    plans = [hd.Plan(f.geometry, grid, S, dtype, max_order=6, dequant_scale=scale, flags=fl | g,
+                     tiling=(16, 16, 1, chunk)) for g in (0, hd.FLAG_FORCE_CHECK)]
+    assert plans[0].info().tiling.chunk == chunk
+    tested = [t.check for t in plans[0].tables()[0]]
+    assert any(tested) and not all(tested)
+    for k in (1, 2, 5):
+        say("rows %s mirror %s order %d" % (dtype, mirror, k))
+        free, forced = (gpu_image(hd, p, arr, k) for p in plans)
+        assert np.array_equal(free, forced)
+        check(rel_l2(free, oracle_image(arr, scale, f.geometry, grid, k)), dtype, "rows %s k=%d" % (dtype, k))
+    for p in plans:
+        p.close()
+
+
 def test_single_element_and_order_above_n(hd):
     f = ph.make_frame(1, 256, 9, 11, n_points=2, seed=4)
     grid = ph.make_grid(9, 11, 3e-3, 5e-3)
