@@ -273,10 +273,11 @@ hodmas_status hodmas_plan_tables(hodmas_plan_t plan, const hodmas_tile_desc** ti
 /* ---------------------------------------------------------------------------
  * Batched form: many frames -- each with its own plan, order and storage type --
  * in one submission.  The library builds a work list of (frame, tile) units,
- * grouped by kind (order x storage type) and sorted by estimated cost within a
- * kind; one persistent kernel per kind present walks its slice with a fixed
- * grid.  A captured graph chains the kernels of all kinds, so one graph launch
- * runs the whole batch.  Each tile runs exactly the per-frame code, so every
+ * grouped by kind (order x storage type x pairing, or several of one storage
+ * type as one mixed kind) and sorted by estimated cost within a kind; one
+ * persistent kernel per kind present walks its slice with a fixed grid.  A
+ * captured graph holds the kernels of all kinds, so one graph launch runs the
+ * whole batch.  Each tile runs exactly the per-frame code, so every
  * frame's image is bitwise the same as from hodmas_beamform with its plan,
  * whatever else is in the batch.  A batch object is used from one stream at a
  * time.
@@ -311,7 +312,9 @@ hodmas_status hodmas_batch_set(hodmas_batch_t batch, const hodmas_plan_t* plans,
                                float* const* images, int32_t n_frames, void* stream);
 
 /* Run the current work list on `stream`: one persistent launch per kind
- * present (kind = order x storage type x mirror pairing). */
+ * present (kind = order x storage type x mirror pairing; unweighted,
+ * compensated frames of one storage type whose kinds would each leave the
+ * device half empty run as one mixed kind). */
 hodmas_status hodmas_batch_launch(hodmas_batch_t batch, void* stream);
 
 /* Build (once) a HIP graph holding the persistent kernels of the kinds in the

@@ -95,6 +95,69 @@ void release(hodmas_batch_s* b)
 
 bool valid_batch(const hodmas_batch_s* b) { return b && b->magic == kBatchMagic; }
 
+struct Unit {
+    int64_t cost;
+    int32_t kind, frame, tile;
+};
+
+// Units a workgroup of a mixed kind takes per draw: one, but where units are
+// short as many as make up half a million slots, which an XCD forms in some
+// 70 ns, the time of a draw, as long as a workgroup still draws four
+// times (256 frames of 128 x 128 at four orders, 64 elements: 470 us one at a
+// time, 325 five at a time).
+int32_t draw_size(int64_t unit_cost, int64_t units, int64_t workgroups)
+{
+    constexpr int64_t kDrawCost = 500000;
+    const int64_t most = workgroups > 0 ? units / (4 * workgroups) : 1;
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>((kDrawCost + unit_cost - 1) / unit_cost, most));
+}
+
+// A mixed kind's n units, in frame and tile order, dealt to `used` XCDs: every
+// frame is cut into that many bands of tile rows of about equal estimated cost,
+// and each XCD takes one of each frame -- another one of the next, as costs
+// that the estimate misses go with depth -- so all have the same mix of orders
+// and record ends whatever those cost.  (Contiguous runs, an XCD all of a few
+// frames, as the kinds of one order are cut, rest on the estimate across orders:
+// 753 us where this takes 685, 24 frames of 17 shapes.)  cut[x] .. cut[x + 1]
+// becomes XCD x's run: its bands, those of the heaviest units first.
+void deal_frames(Unit* run, int n, int used, int32_t* cut, std::vector<Unit>& dealt)
+{
+    struct Band {
+        int64_t unit_cost;
+        int first, end;
+    };
+    std::vector<Band> mine[hodmas::kXcds];
+    for (int f0 = 0, frame = 0; f0 < n; ++frame) {
+        int f1 = f0;
+        int64_t total = 0;
+        for (; f1 < n && run[f1].frame == run[f0].frame; ++f1)
+            total += run[f1].cost;
+        int u = f0;
+        int64_t before = 0;
+        for (int band = 0; band < used; ++band) {
+            const int first = u;
+            const int64_t start = before;
+            // a unit belongs to the band its middle falls in
+            for (; u < f1 && (2 * before + run[u].cost) * used < 2 * total * (band + 1); ++u)
+                before += run[u].cost;
+            if (u > first)
+                mine[(band + frame) % used].push_back({(before - start) / (u - first), first, u});
+        }
+        f0 = f1;
+    }
+    dealt.clear();
+    for (int x = 0; x <= hodmas::kXcds; ++x) {
+        cut[x] = (int32_t)dealt.size();
+        if (x < used) {
+            std::stable_sort(mine[x].begin(), mine[x].end(),
+                             [](const Band& a, const Band& c) { return a.unit_cost > c.unit_cost; });
+            for (const Band& m : mine[x])
+                dealt.insert(dealt.end(), run + m.first, run + m.end);
+        }
+    }
+    std::copy(dealt.begin(), dealt.end(), run);
+}
+
 // Persistent workgroups a kind's kernel launches with: as many as its LDS lets
 // the device hold, cut to its unit count.
 int launch_grid(const hodmas_batch_s* b, int kind)
@@ -181,12 +244,10 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     if (!valid_batch(b) || !plans || !rf || !orders || !images || n_frames < 1 ||
         n_frames > b->max_frames)
         return HODMAS_EINVAL;
-    struct Unit {
-        int64_t cost;
-        int32_t kind, frame, tile;
-    };
     std::vector<Unit> units;
     int64_t pixch = 0;
+    const bool comp = !(b->flags & HODMAS_FLAG_ACC_PLAIN);
+    int64_t unit_cost[3] = {1, 1, 1};       // a mixed kind's mean, by storage type
     int64_t kl[hodmas::kBatchKinds] = {};   // LDS each kind's largest plan needs
     try {
         for (int32_t f = 0; f < n_frames; ++f) {
@@ -228,11 +289,46 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     } catch (const std::bad_alloc&) {
         return HODMAS_ENOMEM;
     }
+    // Kinds of one storage type that come together run as one mixed kind.  Two
+    // kinds of short units are better off as their own kernels, which hold more
+    // waves (eight instead of six) and switch nothing between units: 32 frames
+    // of 128 x 128 at orders 2 and 3 63 us apart and 68 mixed, of 256 x 256 107
+    // and 111; two kinds of longer units (two 512 x 512 frames 90 and 66 us), a
+    // list that barely fills the device once (one 128 x 128 frame 24 and 15), and
+    // three or more kinds (64 such frames at four orders 350 and 325, one at six
+    // 48 and 20) gain.
+    constexpr int64_t kShortUnit = 500000, kOneFill = 1024;   // slots; units
+    if (comp) {
+        for (int dt = 0; dt < 3; ++dt) {
+            auto of_type = [&](int kind) {
+                return kind < hodmas::kOrderKinds && hodmas::kind_dtype(kind) == dt && !hodmas::kind_cf(kind);
+            };
+            int present = 0;
+            for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
+                present += kl[kind] != 0 && of_type(kind);
+            int64_t n = 0, cost = 0;
+            for (const Unit& u : units) {
+                n += of_type(u.kind);
+                cost += of_type(u.kind) ? u.cost : 0;
+            }
+            if (present < 2 || (present == 2 && cost < kShortUnit * n && n > kOneFill))
+                continue;
+            const int mixed = hodmas::mixed_kind(dt);
+            unit_cost[dt] = std::max<int64_t>(1, cost / n);
+            for (Unit& u : units)
+                if (of_type(u.kind))
+                    u.kind = mixed;
+            for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
+                if (of_type(kind)) {
+                    kl[mixed] = std::max(kl[mixed], kl[kind]);
+                    kl[kind] = 0;
+                }
+        }
+    }
     // Each kind runs with the LDS its own plans need, and as many persistent
     // workgroups as that LDS lets a CU hold: one large-LDS plan no longer
     // holds every other kind to its occupancy.
     int kg[hodmas::kBatchKinds] = {};
-    const bool comp = !(b->flags & HODMAS_FLAG_ACC_PLAIN);
     for (int kind = 0; kind < hodmas::kBatchKinds; ++kind) {
         if (kl[kind] == 0)
             continue;
@@ -250,7 +346,9 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
         kg[kind] = b->occ_per_cu[kind] * b->cus;
     }
     // grouped by kind (one persistent kernel each), in frame and tile order
-    std::stable_sort(units.begin(), units.end(), [](const Unit& x, const Unit& y) { return x.kind < y.kind; });
+    auto by_kind = [](const Unit& x, const Unit& y) { return x.kind < y.kind; };
+    if (!std::is_sorted(units.begin(), units.end(), by_kind))
+        std::stable_sort(units.begin(), units.end(), by_kind);
     int32_t kb[hodmas::kBatchKinds] = {}, ke[hodmas::kBatchKinds] = {};
     for (size_t u = 0; u < units.size(); ++u) {
         const int k = units[u].kind;
@@ -266,16 +364,21 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     int32_t cuts[hodmas::kBatchKinds][hodmas::kXcds + 1] = {};
     try {
         std::vector<int64_t> pre;
+        std::vector<Unit> dealt;
         for (int k = 0; k < hodmas::kBatchKinds; ++k) {
             const int n = ke[k] - kb[k];
             if (n <= 0)
                 continue;
             const int used = std::min<int>(hodmas::kXcds, (int)std::min<int64_t>(kg[k], n));
             Unit* run = units.data() + kb[k];
+            int32_t* cut = cuts[k];
+            if (k >= hodmas::kOrderKinds) {
+                deal_frames(run, n, used, cut, dealt);
+                continue;
+            }
             pre.assign((size_t)n + 1, 0);
             for (int u = 0; u < n; ++u)
                 pre[u + 1] = pre[u] + run[u].cost;
-            int32_t* cut = cuts[k];
             for (int x = 1; x < used; ++x) {
                 const int64_t target = pre[n] * x / used;
                 int i = (int)(std::lower_bound(pre.begin(), pre.end(), target) - pre.begin());
@@ -305,6 +408,10 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     std::memcpy(hdr->begin, kb, sizeof(kb));
     std::memcpy(hdr->end, ke, sizeof(ke));
     std::memcpy(hdr->xcd, cuts, sizeof(cuts));
+    for (int dt = 0; dt < 3; ++dt) {
+        const int k = hodmas::mixed_kind(dt);
+        hdr->per_draw[dt] = draw_size(unit_cost[dt], ke[k] - kb[k], std::min<int64_t>(kg[k], ke[k] - kb[k]));
+    }
     std::memcpy(b->begin, hdr->begin, sizeof(b->begin));
     std::memcpy(b->end, hdr->end, sizeof(b->end));
     std::memcpy(b->kind_lds, kl, sizeof(kl));
@@ -314,6 +421,7 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
         frames[f].args = hodmas::frame_args(plans[f], rf[f], images[f]);
         frames[f].order = orders[f];
         frames[f].dtype = plans[f]->rf.dtype;
+        frames[f].pairing = (plans[f]->flags & HODMAS_FLAG_MIRROR) ? 2 : 1;
     }
     for (size_t u = 0; u < units.size(); ++u)
         list[u] = BatchUnit{units[u].frame, units[u].tile};

@@ -45,7 +45,7 @@ struct OrderImages {
 // Work list of the persistent batched kernels (device memory).  Units are
 // grouped by kind = (coherence weighting, order, storage type, pixels per
 // delay: 1, or 2 for mirror pairs); kind k owns units [begin[k], end[k]).
-constexpr int kBatchKinds = 2 * HODMAS_MAX_ORDER * 3 * 2;
+constexpr int kOrderKinds = 2 * HODMAS_MAX_ORDER * 3 * 2;
 constexpr int batch_kind(int order, int dtype, int pairing, int cf)
 {
     return ((cf * HODMAS_MAX_ORDER + order - 1) * 3 + dtype) * 2 + pairing - 1;
@@ -54,10 +54,15 @@ constexpr int kind_order(int kind) { return kind / 6 % HODMAS_MAX_ORDER + 1; }
 constexpr int kind_dtype(int kind) { return kind / 2 % 3; }
 constexpr int kind_pairing(int kind) { return kind % 2 + 1; }
 constexpr int kind_cf(int kind) { return kind / (6 * HODMAS_MAX_ORDER); }
-static_assert(batch_kind(kind_order(kBatchKinds - 1), kind_dtype(kBatchKinds - 1), kind_pairing(kBatchKinds - 1),
-                         kind_cf(kBatchKinds - 1)) == kBatchKinds - 1 &&
+static_assert(batch_kind(kind_order(kOrderKinds - 1), kind_dtype(kOrderKinds - 1), kind_pairing(kOrderKinds - 1),
+                         kind_cf(kOrderKinds - 1)) == kOrderKinds - 1 &&
                   batch_kind(kind_order(40), kind_dtype(40), kind_pairing(40), kind_cf(40)) == 40,
               "kind decoding");
+// ... and one kind per storage type whose kernel forms units of any order and
+// pairing (unweighted, compensated): a work list of several kinds that are
+// each too small to fill the device runs as one.
+constexpr int mixed_kind(int dtype) { return kOrderKinds + dtype; }
+constexpr int kBatchKinds = kOrderKinds + 3;
 
 constexpr int kXcds = 8;                    // workgroup b runs on XCD b mod 8
 
@@ -70,13 +75,18 @@ struct BatchHeader {
     int32_t begin[kBatchKinds];
     int32_t end[kBatchKinds];
     int32_t xcd[kBatchKinds][kXcds + 1];
+    // draws so far from each run of a mixed kind (its kernel counts; zero in a
+    // new work list and after each launch)
+    int32_t drawn[3][kXcds];
+    int32_t per_draw[3];      // units per draw of a mixed kind
 };
 
 struct BatchFrame {
     FrameArgs args;
     int32_t order;
     int32_t dtype;
-    int32_t pad[2];
+    int32_t pairing;
+    int32_t pad;
 };
 
 // tile: the tile to form, or for a mirror-pair kind the pair's left tile

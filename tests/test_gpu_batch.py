@@ -284,3 +284,38 @@ def test_graph_gains_kinds_after_capture(hd):
     batch.close()
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "i16"])
+@pytest.mark.parametrize("tiling,frames", [((8, 8, 4, 0), 150), ((16, 16, 1, 0), 48), (None, 5)])
+def test_mixed_orders_in_one_kernel(hd, dtype, tiling, frames):
+    """Frames of all orders, paired and unpaired, in one list: short units that
+    are drawn several at a time, longer ones, and a list smaller than the
+    device.  Every image equals its own launch on each of several launches and
+    replays of the same list (the draws start from zero each time) and after
+    the list changes."""
+    f = ph.make_frame(24, 500, 64, 64, n_points=5, snr_db=15.0, seed=71)
+    grid = ph.make_grid(64, 64, 24 * 0.3e-3, 9e-3)
+    arr = {"f32": ph.to_fp32, "f16": ph.to_fp16}.get(dtype, lambda r: ph.to_int16(r, 71)[0])(f.rf)
+    scale = float(ph.to_int16(f.rf, 71)[1]) if dtype == "i16" else 1.0
+    rf = torch.from_numpy(np.ascontiguousarray(arr)).cuda()
+    two = [hd.Plan(f.geometry, grid, 500, dtype, max_order=6, dequant_scale=scale, tiling=tiling, flags=fl)
+           for fl in (0, hd.FLAG_MIRROR)]
+    own = {(i, k): two[i].beamform(rf, k).clone() for i in (0, 1) for k in range(1, 7)}
+    picks = [(i % 2, i // 2 % 6 + 1) for i in range(frames)]
+    outs = [torch.empty((64, 64), device="cuda") for _ in picks]
+    units = sum(p.info().n_tiles for p in two) * frames
+    bt = hd.Batch(frames, units, max(p.info().lds_bytes for p in two))
+    for part in (picks, picks[: frames // 2], picks):
+        bt.set([two[i] for i, _ in part], [rf] * len(part), [k for _, k in part], outs[: len(part)])
+        bt.capture()
+        for go in (bt.launch, bt.replay, bt.launch, bt.replay):
+            for o in outs:
+                o.fill_(float("nan"))
+            go()
+            torch.cuda.synchronize()
+            for o, p in zip(outs, part):
+                assert torch.equal(o, own[p]), (p, go.__name__)
+    bt.close()
+    for p in two:
+        p.close()
