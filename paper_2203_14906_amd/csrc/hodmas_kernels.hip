@@ -248,9 +248,9 @@ __device__ __forceinline__ int zero_offset(int window) { return window * 4; }
 __device__ __forceinline__ int mirror_offset(int nch, int window) { return nch * row_stride(window) * 4; }
 
 // The rows a wave stages are a contiguous run of the chunk's; lane j holds the
-// table entry of the run's row c + j.  One vector load brings 64 rows'
-// entries; those of the first 64 are requested a chunk ahead, with the rows of
-// the chunk before, so that a chunk's staging starts with its rows' loads.
+// table entry of the run's row c + j, so one vector load brings 64 rows'
+// entries.  (Requesting a chunk's entries with the rows of the chunk before
+// gained nothing and cost short units 2 %.)
 // A row inside the record needs the byte offset in the frame of LDS window
 // position 0, in `at`; others (CHECK) its index in the record, and the record.
 struct Rows {
@@ -273,7 +273,7 @@ template <int DT, int M, bool CHECK>
 __device__ __forceinline__ Rows load_rows(const FrameArgs& A, ConstStage st, int nch, RowRun run, int c, int lane)
 {
     const Global<const int> ent = global_ptr(reinterpret_cast<const int*>(st));
-    const int j = max(min(c + lane, run.s1 - 1), 0);
+    const int j = min(c + lane, run.s1 - 1);
     const bool mirrored = M == 2 && j >= nch;
     const int src = mirrored ? j - nch : j;
     const int elem = ent[2 * src];
@@ -297,15 +297,14 @@ __device__ __forceinline__ Rows load_rows(const FrameArgs& A, ConstStage st, int
 // clamped sample only as the neighbour of the record's last one, with weight
 // zero, and every other delay is pointed at the zero pair (redirect).
 // Measured against int16 rows, and rows at the record ends, through registers
-// (sixteen loads, a wait, conversions and LDS stores at a time), with a wave's
-// table entries requested a chunk ahead: int16, 256 elements, 4096 samples,
+// (sixteen loads, a wait, conversions and LDS stores at a time): int16, 256 elements, 4096 samples,
 // mirror pairs at order 1, 256 x 256 60 -> 42 us, 512 x 512 62 -> 53 us; 1024 x
 // 1024, 2048 samples, order 6 225 -> 220 us; a 331 x 203 image of 96 elements
 // whose far half runs past the record 14.7 -> 13.3 us; 16 mixed frames as one
 // batch 473 -> 434 us.
 template <int DT, int M, bool CHECK>
-__device__ __forceinline__ void stage_direct(const FrameArgs& A, ConstStage st, Rows r, int nch, RowRun run,
-                                             int window, float* __restrict__ lds, int lane)
+__device__ __forceinline__ void stage_direct(const FrameArgs& A, ConstStage st, int nch, RowRun run, int window,
+                                             float* __restrict__ lds, int lane)
 {
     constexpr int esz = DT == HODMAS_F32 ? 4 : 2;
     using LdsPtr = __attribute__((address_space(3))) void*;
@@ -318,8 +317,7 @@ __device__ __forceinline__ void stage_direct(const FrameArgs& A, ConstStage st, 
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LdsPtr)(lds + row * stride + b), 2, voff, soff, 0, 0);
     };
     for (int c = run.s0; c < run.s1; c += 64) {
-        if (c > run.s0)
-            r = load_rows<DT, M, CHECK>(A, st, nch, run, c, lane);
+        const Rows r = load_rows<DT, M, CHECK>(A, st, nch, run, c, lane);
         const int cend = __builtin_amdgcn_readfirstlane(min(run.s1 - c, 64));
         if constexpr (CHECK) {
             const char* rf = static_cast<const char*>(A.rf);
@@ -367,10 +365,9 @@ __device__ __forceinline__ void widen_codes(float* __restrict__ lds, int begin, 
     }
 }
 
-// One chunk's rows into LDS; `r` holds the wave's first rows on entry and
-// those of the next chunk (from st + nch, `next` slots of it) on return.
+// One chunk's rows into LDS.
 template <int DT, int M, bool CHECK>
-__device__ __forceinline__ void stage_chunk(const FrameArgs& A, ConstStage st, Rows& r, int nch, int next, int window,
+__device__ __forceinline__ void stage_chunk(const FrameArgs& A, ConstStage st, int nch, int window,
                                             float* __restrict__ lds, int wave, int nwaves, int lane)
 {
     const RowRun run = row_run<M>(nch, wave, nwaves);
@@ -388,11 +385,7 @@ __device__ __forceinline__ void stage_chunk(const FrameArgs& A, ConstStage st, R
                 lds[row * stride + window + lane] = 0.f;
         }
     }
-    stage_direct<DT, M, CHECK>(A, st, r, nch, run, window, lds, lane);
-    if (next > 0) [[unlikely]] {     // most tiles of small windows take one chunk
-        const RowRun after = row_run<M>(next, wave, nwaves);
-        r = load_rows<DT, M, CHECK>(A, st + nch, next, after, after.s0, lane);
-    }
+    stage_direct<DT, M, CHECK>(A, st, nch, run, window, lds, lane);
     __builtin_amdgcn_s_waitcnt(0);   // the copies are in LDS before the caller's barrier
     if constexpr (DT == HODMAS_I16)
         widen_codes(lds, run.s0 * stride, run.s1 * stride, A.in_scale, lane);
@@ -825,14 +818,10 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
         acc[mm].clear();
     ConstEntry E = A.entries + td.first_entry;
     ConstStage St = A.stage + td.first_entry;
-    const int nch0 = min(A.chunk, td.n_active);
-    const RowRun run0 = row_run<M>(nch0, wave, nwaves);
-    Rows rows = load_rows<DT, M, CHECK>(A, St, nch0, run0, run0.s0, lane);
     for (int c0 = 0; c0 < td.n_active; c0 += A.chunk) {
         const int nch = min(A.chunk, td.n_active - c0);
         __syncthreads();                       // previous readers of the LDS are done
-        stage_chunk<DT, M, CHECK>(A, St + c0, rows, nch, min(A.chunk, td.n_active - c0 - nch), td.window, lds, wave,
-                                  nwaves, lane);
+        stage_chunk<DT, M, CHECK>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
         __syncthreads();
         if (c0 == 0)
             staged();
@@ -1294,16 +1283,10 @@ __device__ __forceinline__ void orders_tile(const FrameArgs& A, const OrderImage
     }
     ConstEntry E = A.entries + td.first_entry;
     ConstStage St = A.stage + td.first_entry;
-    const int nch0 = min(A.chunk, td.n_active);
-    const RowRun run0 = row_run<1>(nch0, wave, nwaves);
-    Rows rows{0, 0};
-    if (nch0 > 0)
-        rows = load_rows<DT, 1, CHECK>(A, St, nch0, run0, run0.s0, lane);
     for (int c0 = 0; c0 < td.n_active; c0 += A.chunk) {
         const int nch = min(A.chunk, td.n_active - c0);
         __syncthreads();
-        stage_chunk<DT, 1, CHECK>(A, St + c0, rows, nch, min(A.chunk, td.n_active - c0 - nch), td.window, lds, wave,
-                                  nwaves, lane);
+        stage_chunk<DT, 1, CHECK>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
         __syncthreads();
         int goff = 0;
         for (int h = 0; h < g; ++h)
