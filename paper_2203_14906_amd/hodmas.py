@@ -191,6 +191,15 @@ def _load():
 
 lib = _load()
 
+try:
+    import torch as _torch
+    _TORCH_DT = {F32: _torch.float32, F16: _torch.float16, I16: _torch.int16}
+    # the current stream's handle without a torch.cuda.Stream around it (the
+    # object costs 2.7 us of a 9 us call)
+    _raw_stream = getattr(_torch._C, "_cuda_getCurrentRawStream", None)
+except ImportError:      # plans without a device need no torch
+    _torch, _TORCH_DT, _raw_stream = None, {}, None
+
 
 def status_string(status: int) -> str:
     return lib.hodmas_status_string(int(status)).decode()
@@ -207,11 +216,12 @@ def _check(status, what):
 
 def _stream_handle(stream):
     if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _raw_stream is not None:
+            return _raw_stream(_torch.cuda.current_device())
+        return _torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _c_structs(geometry, grid, n_samples, dtype, dequant_scale, frame_max, channel_stride):
@@ -295,35 +305,32 @@ class Plan:
     def beamform(self, rf, order, out=None, stream=None):
         """Beamform ``rf`` (device tensor [N][stride] of the plan's dtype) at
         ``order`` into ``out`` (device float32 [nz][nx]); returns ``out``."""
-        import torch
         if out is None:
-            out = torch.empty((self.nz, self.nx), dtype=torch.float32, device=rf.device)
+            out = _torch.empty((self.nz, self.nx), dtype=_torch.float32, device=rf.device)
         _check_tensor(rf, self)
-        if out.dtype != torch.float32 or not out.is_contiguous() or out.numel() != self.nx * self.nz:
+        if out.dtype != _torch.float32 or not out.is_contiguous() or out.numel() != self.nx * self.nz:
             raise ValueError("out must be a contiguous float32 tensor of nz*nx elements")
         if not out.is_cuda:
             raise ValueError("out must live on the GPU")
-        _check(lib.hodmas_beamform(self._h, ctypes.c_void_p(rf.data_ptr()), int(order),
-                                   ctypes.c_void_p(out.data_ptr()), _stream_handle(stream)),
+        _check(lib.hodmas_beamform(self._h, rf.data_ptr(), int(order), out.data_ptr(), _stream_handle(stream)),
                "hodmas_beamform")
         return out
 
     def beamform_orders(self, rf, max_order, outs=None, stream=None):
         """Orders 1..max_order of ``rf`` in one pass; returns the list of images
         (``outs[k-1]`` receives order k)."""
-        import torch
         _check_tensor(rf, self)
         if outs is None:
-            outs = [torch.empty((self.nz, self.nx), dtype=torch.float32, device=rf.device)
+            outs = [_torch.empty((self.nz, self.nx), dtype=_torch.float32, device=rf.device)
                     for _ in range(max_order)]
         if len(outs) < max_order:
             raise ValueError("need one output image per order")
         for o in outs[:max_order]:
-            if o.dtype != torch.float32 or not o.is_contiguous() or o.numel() != self.nx * self.nz or not o.is_cuda:
+            if o.dtype != _torch.float32 or not o.is_contiguous() or o.numel() != self.nx * self.nz or not o.is_cuda:
                 raise ValueError("each output must be a contiguous float32 GPU tensor of nz*nx elements")
         ptrs = (ctypes.c_void_p * max_order)(*[o.data_ptr() for o in outs[:max_order]])
-        _check(lib.hodmas_beamform_orders(self._h, ctypes.c_void_p(rf.data_ptr()), int(max_order), ptrs,
-                                          _stream_handle(stream)), "hodmas_beamform_orders")
+        _check(lib.hodmas_beamform_orders(self._h, rf.data_ptr(), int(max_order), ptrs, _stream_handle(stream)),
+               "hodmas_beamform_orders")
         return outs[:max_order]
 
     def close(self):
@@ -354,7 +361,7 @@ class Batch:
             raise ValueError("plans, rfs, orders and images must have the same length")
         for p, r, o in zip(plans, rfs, images):
             _check_tensor(r, p)
-            if not o.is_cuda or o.dtype.__str__() != "torch.float32" or not o.is_contiguous() or \
+            if not o.is_cuda or o.dtype != _torch.float32 or not o.is_contiguous() or \
                     o.numel() != p.nx * p.nz:
                 raise ValueError("each image must be a contiguous float32 GPU tensor of nz*nx elements")
         ph = (ctypes.c_void_p * n)(*[p.handle.value for p in plans])
@@ -392,19 +399,15 @@ class Batch:
             pass
 
 
-_TORCH_DT = {F32: "float32", F16: "float16", I16: "int16"}
-
-
 def _check_tensor(rf, plan):
-    import torch
     if not rf.is_cuda:
         raise ValueError("rf must live on the GPU")
-    if str(rf.dtype).split(".")[-1] != _TORCH_DT[plan.dtype]:
-        raise ValueError("rf dtype %s does not match the plan (%s)" % (rf.dtype, _TORCH_DT[plan.dtype]))
+    if rf.dtype != _TORCH_DT[plan.dtype]:
+        raise ValueError("rf dtype %s does not match the plan (%s)"
+                         % (rf.dtype, str(_TORCH_DT[plan.dtype]).split(".")[-1]))
     if rf.dim() != 2 or rf.shape[0] != plan.n_elements or rf.stride(1) != 1 or \
             rf.stride(0) != plan.channel_stride or rf.shape[1] < plan.n_samples:
         raise ValueError("rf must be [n_elements][>= n_samples] with row stride %d" % plan.channel_stride)
-    return torch
 
 
 def _display_desc(nx, nz, dz_m, sound_speed_m_s, f_lo_hz, f_hi_hz, numtaps, dynamic_range_db):
@@ -451,18 +454,19 @@ class Display:
         self._h = ctypes.c_void_p()
         _check(lib.hodmas_display_plan(ctypes.byref(d), ctypes.byref(self._h)), "hodmas_display_plan")
 
+    def _check_images(self, tensors):
+        for t in tensors:
+            if t is not None and (t.dtype != _torch.float32 or not t.is_cuda or not t.is_contiguous()
+                                  or t.shape != (self.nz, self.nx)):
+                raise ValueError("images must be contiguous float32 GPU tensors [nz][nx]")
+
     def run(self, image, envelope=None, db=None, stream=None):
         """Returns (envelope or None, dB image); allocates outputs not given."""
-        import torch
-        for t in (image, envelope, db):
-            if t is not None and (t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous()
-                                  or tuple(t.shape) != (self.nz, self.nx)):
-                raise ValueError("images must be contiguous float32 GPU tensors [nz][nx]")
+        self._check_images((image, envelope, db))
         if db is None:
-            db = torch.empty_like(image)
-        _check(lib.hodmas_display_run(self._h, ctypes.c_void_p(image.data_ptr()),
-                                      ctypes.c_void_p(envelope.data_ptr()) if envelope is not None else None,
-                                      ctypes.c_void_p(db.data_ptr()), _stream_handle(stream)),
+            db = _torch.empty_like(image)
+        _check(lib.hodmas_display_run(self._h, image.data_ptr(), envelope.data_ptr() if envelope is not None else None,
+                                      db.data_ptr(), _stream_handle(stream)),
                "hodmas_display_run")
         return envelope, db
 
@@ -470,16 +474,12 @@ class Display:
         """The chain over a list of images of this shape (up to 16 per launch
         pair).  Returns (envelopes or None, dB images); allocates the dB
         images not given."""
-        import torch
         n = len(images)
         if n < 1 or (envelopes is not None and len(envelopes) != n) or (dbs is not None and len(dbs) != n):
             raise ValueError("images, envelopes and dbs must be non-empty lists of one length")
         if dbs is None:
-            dbs = [torch.empty_like(im) for im in images]
-        for t in list(images) + list(dbs) + list(envelopes or []):
-            if t is not None and (t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous()
-                                  or tuple(t.shape) != (self.nz, self.nx)):
-                raise ValueError("images must be contiguous float32 GPU tensors [nz][nx]")
+            dbs = [_torch.empty_like(im) for im in images]
+        self._check_images(list(images) + list(dbs) + list(envelopes or []))
         arr = ctypes.c_void_p * n
         pi = arr(*[im.data_ptr() for im in images])
         pd = arr(*[d.data_ptr() for d in dbs])
