@@ -1,7 +1,8 @@
 // Batched form: a work list of (frame, tile) units over many frames, grouped by
-// kind (order x storage type x mirror pairing x coherence weighting) and walked by one persistent
-// kernel per kind; a HIP graph holds the kernels so one graph launch runs the
-// batch.
+// kind (order x storage type x mirror pairing x coherence weighting, or several
+// orders and pairings of one storage type as one mixed kind) and walked by one
+// persistent kernel per kind; a HIP graph holds the kernels so one graph launch
+// runs the batch.
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
