@@ -215,7 +215,7 @@ const char* hodmas_status_string(hodmas_status status);
  * With HODMAS_FLAG_TUNE_BATCH (unless HODMAS_FLAG_CF comes with
  * HODMAS_FLAG_ACC_PLAIN, which no batch runs) each candidate is timed
  * the way a batch runs it: copies of the frame, each with its own image, in
- * one persistent batched launch of up to 256 copies -- enough work units to
+ * one batched launch of up to 256 copies -- enough work units to
  * fill the device -- and the time per copy is compared.
  * Allocates and frees scratch device memory; not for the hot path.
  * Errors: EINVAL, ENOMEM, EDEVICE, EUNSUPPORTED (no candidate could run). */
@@ -275,7 +275,7 @@ hodmas_status hodmas_plan_tables(hodmas_plan_t plan, const hodmas_tile_desc** ti
  * in one submission.  The library builds a work list of (frame, tile) units,
  * grouped by kind (order x storage type x pairing, or several of one storage
  * type as one mixed kind) and sorted by estimated cost within a kind; one
- * persistent kernel per kind present walks its slice with a fixed grid.  A
+ * kernel per kind present walks its slice.  A
  * captured graph holds the kernels of all kinds, so one graph launch runs the
  * whole batch.  Each tile runs exactly the per-frame code, so every
  * frame's image is bitwise the same as from hodmas_beamform with its plan,
@@ -288,8 +288,8 @@ typedef struct hodmas_batch_s* hodmas_batch_t;
  * units (a HODMAS_FLAG_MIRROR plan's units are its n_tiles / 2 mirror pairs),
  * on the current HIP device.  max_lds_bytes bounds the LDS any member
  * plan may need (0: the largest a workgroup can have).  Each kind of a work
- * list runs with the LDS of its own largest plan and as many persistent
- * workgroups as that LDS leaves room for.  flags: HODMAS_FLAG_ACC_PLAIN or 0;
+ * list runs with the LDS of its own largest plan and as many
+ * workgroups at once as that LDS leaves room for.  flags: HODMAS_FLAG_ACC_PLAIN or 0;
  * member plans must match it.  Errors: EINVAL, ENOMEM, EDEVICE. */
 hodmas_status hodmas_batch_create(int32_t max_frames, int64_t max_units, int64_t max_lds_bytes,
                                   uint32_t flags, hodmas_batch_t* out);
@@ -311,21 +311,21 @@ hodmas_status hodmas_batch_set(hodmas_batch_t batch, const hodmas_plan_t* plans,
                                const void* const* rf, const int32_t* orders,
                                float* const* images, int32_t n_frames, void* stream);
 
-/* Run the current work list on `stream`: one persistent launch per kind
+/* Run the current work list on `stream`: one launch per kind
  * present (kind = order x storage type x mirror pairing; unweighted,
  * compensated frames of one storage type whose kinds would each leave the
  * device half empty run as one mixed kind). */
 hodmas_status hodmas_batch_launch(hodmas_batch_t batch, void* stream);
 
-/* Build (once) a HIP graph holding the persistent kernels of the kinds in the
+/* Build (once) a HIP graph holding the kernels of the kinds in the
  * current work list (every kind when no list is set yet), with no order
  * between them (kinds write disjoint images, so one kind's tail overlaps the
  * next kind's start); they read the work list from device memory, so later
  * hodmas_batch_set calls with those kinds need no re-capture.
  * hodmas_batch_replay launches that graph on `stream`, after fitting the
  * instantiated graph to the current work list: kinds absent from it are
- * switched off and each present kind gets its own LDS size and persistent
- * grid, at most one workgroup per unit; a kind the graph has no kernel for
+ * switched off and each present kind gets its own LDS size and
+ * grid; a kind the graph has no kernel for
  * has the graph rebuilt with every kind seen so far.  When that changes a
  * node, the replay first waits for the previous replay of the graph to
  * finish (host-side); replays of an unchanged kind mix do not wait. */
@@ -336,7 +336,7 @@ hodmas_status hodmas_batch_replay(hodmas_batch_t batch, void* stream);
 typedef struct {
     int32_t n_frames;
     int64_t n_units;
-    int32_t grid;                /* persistent workgroups (largest over the kinds present) */
+    int32_t grid;                /* workgroups the device holds at once (largest over the kinds present) */
     int64_t lds_bytes;           /* dynamic LDS per workgroup (largest over the kinds present) */
     int64_t pixel_channels;      /* sum over frames of nx*nz*N */
 } hodmas_batch_info;

@@ -1,7 +1,7 @@
 // Batched form: a work list of (frame, tile) units over many frames, grouped by
 // kind (order x storage type x mirror pairing x coherence weighting, or several
 // orders and pairings of one storage type as one mixed kind) and walked by one
-// persistent kernel per kind; a HIP graph holds the kernels so one graph launch
+// kernel per kind; a HIP graph holds the kernels so one graph launch
 // runs the batch.
 #include <hip/hip_runtime_api.h>
 
@@ -38,11 +38,12 @@ struct hodmas_batch_s {
     int64_t lds_bytes = 0;
     uint32_t flags = 0;
     int cus = 0;                          // compute units of the device
-    int grid[hodmas::kBatchKinds] = {};   // persistent workgroups per kind at lds_bytes
+    int grid[hodmas::kBatchKinds] = {};   // workgroups the device holds per kind at lds_bytes
     // the current work list's kinds: LDS of their largest member plan and the
-    // persistent grid that LDS allows
+    // workgroups the device holds at that LDS
     int64_t kind_lds[hodmas::kBatchKinds] = {};
     int kind_grid[hodmas::kBatchKinds] = {};
+    int32_t longest[hodmas::kBatchKinds] = {};   // units of the longest XCD run
     // the last occupancy answer per kind (a serving loop sets a list per launch)
     int64_t occ_lds[hodmas::kBatchKinds] = {};
     int occ_per_cu[hodmas::kBatchKinds] = {};
@@ -159,10 +160,22 @@ void deal_frames(Unit* run, int n, int used, int32_t* cut, std::vector<Unit>& de
     std::copy(dealt.begin(), dealt.end(), run);
 }
 
-// Persistent workgroups a kind's kernel launches with: as many as its LDS lets
-// the device hold, cut to its unit count.
+// Workgroups a kind's kernel launches with.  The kernels of one order take one
+// per unit: the device hands a workgroup out as another ends, which evens out
+// better than fixed shares of a grid that just fills the device.  Measured so,
+// and with fixed shares: one unpaired 2048 x 2048 frame from 256 elements at
+// order 1 501 and 659 us, at order 6 789 and 917; one of 512 x 512 from 128 at
+// order 2 28.8 and 39.5; eight of them at order 6, paired, 187 and 191; at order
+// 1 90 and 89; 256 of 128 x 128 at order 1 264 and 309.  From kMostWorkgroups on
+// each takes several (1100 of 128 x 128, 70400 units: 1031 and 1254 us).  A
+// mixed kind's kernel, which draws its units, runs as many workgroups as its
+// LDS lets the device hold, cut to its unit count: it evens out by drawing, and
+// starting it once per unit costs more (24 float16 frames 712 against 685 us).
 int launch_grid(const hodmas_batch_s* b, int kind)
 {
+    constexpr int kMostWorkgroups = 1 << 16;
+    if (kind < hodmas::kOrderKinds)
+        return (int)std::min<int64_t>((int64_t)b->longest[kind] * hodmas::kXcds, kMostWorkgroups);
     return (int)std::min<int64_t>(b->kind_grid[kind], b->end[kind] - b->begin[kind]);
 }
 
@@ -267,7 +280,7 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
             if (p->lds_bytes > b->lds_bytes)
                 return HODMAS_EINVAL;
             if (p->tiling.tile_x * p->tiling.tile_z * p->tiling.split != hodmas::kBlock)
-                return HODMAS_EINVAL;   // the persistent kernels run 256-thread tiles
+                return HODMAS_EINVAL;   // the batched kernels run 256-thread tiles
             // a mirror plan's units are the pairs: each left-half tile with its mirror
             const int pairing = (p->flags & HODMAS_FLAG_MIRROR) ? 2 : 1;
             const int n_units = (int)p->tiles.size() / pairing;
@@ -293,11 +306,12 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     // Kinds of one storage type that come together run as one mixed kind.  Two
     // kinds of short units are better off as their own kernels, which hold more
     // waves (eight instead of six) and switch nothing between units: 32 frames
-    // of 128 x 128 at orders 2 and 3 63 us apart and 68 mixed, of 256 x 256 107
-    // and 111; two kinds of longer units (two 512 x 512 frames 90 and 66 us), a
-    // list that barely fills the device once (one 128 x 128 frame 24 and 15), and
-    // three or more kinds (64 such frames at four orders 350 and 325, one at six
-    // 48 and 20) gain.
+    // of 128 x 128 at orders 2 and 3 55 us apart and 68 mixed, of 256 x 256 100
+    // and 111; two kinds of longer units (four paired 512 x 512 frames 70 and 66
+    // us launched, 93 and 72 replayed), a list that barely fills the device once
+    // (two paired 128 x 128 frames 23 and 12), and three or more kinds (64 such
+    // frames at four orders 76 and 72, replayed 154 and 78; six at six 49 and 15)
+    // gain or lose little.
     constexpr int64_t kShortUnit = 500000, kOneFill = 1024;   // slots; units
     if (comp) {
         for (int dt = 0; dt < 3; ++dt) {
@@ -326,9 +340,9 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
                 }
         }
     }
-    // Each kind runs with the LDS its own plans need, and as many persistent
-    // workgroups as that LDS lets a CU hold: one large-LDS plan no longer
-    // holds every other kind to its occupancy.
+    // Each kind runs with the LDS its own plans need, and with as many
+    // workgroups at once as that LDS lets a CU hold: one large-LDS plan does
+    // not hold every other kind to its occupancy.
     int kg[hodmas::kBatchKinds] = {};
     for (int kind = 0; kind < hodmas::kBatchKinds; ++kind) {
         if (kl[kind] == 0)
@@ -346,7 +360,7 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
         }
         kg[kind] = b->occ_per_cu[kind] * b->cus;
     }
-    // grouped by kind (one persistent kernel each), in frame and tile order
+    // grouped by kind (one kernel each), in frame and tile order
     auto by_kind = [](const Unit& x, const Unit& y) { return x.kind < y.kind; };
     if (!std::is_sorted(units.begin(), units.end(), by_kind))
         std::stable_sort(units.begin(), units.end(), by_kind);
@@ -409,6 +423,11 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     std::memcpy(hdr->begin, kb, sizeof(kb));
     std::memcpy(hdr->end, ke, sizeof(ke));
     std::memcpy(hdr->xcd, cuts, sizeof(cuts));
+    for (int k = 0; k < hodmas::kBatchKinds; ++k) {
+        b->longest[k] = 0;
+        for (int x = 0; x < hodmas::kXcds; ++x)
+            b->longest[k] = std::max(b->longest[k], cuts[k][x + 1] - cuts[k][x]);
+    }
     for (int dt = 0; dt < 3; ++dt) {
         const int k = hodmas::mixed_kind(dt);
         hdr->per_draw[dt] = draw_size(unit_cost[dt], ke[k] - kb[k], std::min<int64_t>(kg[k], ke[k] - kb[k]));
@@ -479,8 +498,8 @@ hodmas_status hodmas_batch_launch(hodmas_batch_t b, void* stream)
 // absent kinds: every node of a graph launch costs time even when switched
 // off.  Before each replay the nodes are fitted to the current work list in
 // the instantiated graph itself: a kind that is absent is switched off, and a
-// present kind runs with the LDS its own plans need and the persistent grid
-// that LDS allows, cut to its unit count.
+// present kind runs with the LDS its own plans need and the grid of its units
+// (launch_grid).
 namespace {
 
 hipKernelNodeParams node_params(const hodmas_batch_s* b, int kind, int grid, int64_t lds, void** args)

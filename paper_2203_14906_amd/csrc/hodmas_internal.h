@@ -42,7 +42,7 @@ struct OrderImages {
     float* img[HODMAS_MAX_ORDER];
 };
 
-// Work list of the persistent batched kernels (device memory).  Units are
+// Work list of the batched kernels (device memory).  Units are
 // grouped by kind = (coherence weighting, order, storage type, pixels per
 // delay: 1, or 2 for mirror pairs); kind k owns units [begin[k], end[k]).
 constexpr int kOrderKinds = 2 * HODMAS_MAX_ORDER * 3 * 2;
@@ -149,7 +149,7 @@ FrameArgs frame_args(const hodmas_plan_s* plan, const void* rf_dev, float* image
 int launch_orders(const FrameArgs& a, const OrderImages& out, int kmax, int dtype, bool compensated,
                   int64_t lds_bytes, void* stream);
 
-// The persistent batched kernel of one kind (for graph nodes) and a launch of
+// The batched kernel of one kind (for graph nodes) and a launch of
 // it.  Coherence-weighted kinds exist for compensated accumulation only
 // (batch_kernel returns null for the others).
 const void* batch_kernel(int kind, bool compensated);

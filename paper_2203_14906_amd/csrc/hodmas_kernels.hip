@@ -921,13 +921,15 @@ __global__ __launch_bounds__(kMaxBlock) void hodmas_frame_kernel(FrameArgs A)
     }
 }
 
-// Persistent form: one kernel per (order, storage type, pairing, coherence
-// weighting).  Its fixed grid walks that kind's slice of the batch's work
+// Batched form: one kernel per (order, storage type, pairing, coherence
+// weighting).  Its grid walks that kind's slice of the batch's work
 // list -- (frame, tile) units of many frames with their own plans.  The slice
 // is cut into one run per XCD (neighbouring tiles of one or a few frames, of
 // about equal estimated cost, each sorted by cost); the g workgroups on XCD x
-// (workgroups x, x+8, ...) walk run x, the l-th of them taking units l,
-// 2g-1-l, 2g+l, ... (a snake, which evens out the per-workgroup cost).  With
+// (workgroups x, x+8, ...) walk run x, the l-th of them taking unit l.  A grid
+// has one workgroup per unit of the longest run; only in lists beyond the
+// largest grid does the l-th go on to units 2g-1-l, 2g+l, ... (a snake, which
+// evens out the per-workgroup cost).  With
 // M == 2 a unit is a mirror pair, named by its left tile.  Each unit runs
 // exactly the code of the per-frame kernel, so a frame's image does not depend
 // on what else is in the batch.

@@ -13,7 +13,7 @@
 
 namespace {
 
-// Batch-mode timing: copies of the frame per persistent launch -- enough units
+// Batch-mode timing: copies of the frame per batched launch -- enough units
 // (quarter-size tiles as the unit estimate) to fill the device, within an
 // image budget.
 constexpr int64_t kTuneBatchCopies = 256;
@@ -109,7 +109,7 @@ extern "C" hodmas_status hodmas_autotune(const hodmas_geometry* geometry, const 
     const size_t rf_bytes = esz * (size_t)rf->channel_stride * (size_t)geometry->n_elements;
     const size_t img_bytes = 4 * (size_t)grid->nx * (size_t)grid->nz;
     // A batch member is timed the way a batch runs it: enough copies of the
-    // frame in one persistent launch to fill the device (a single small frame
+    // frame in one batched launch to fill the device (a single small frame
     // would favour tilings that split elements for parallelism, which a
     // batch does not need), each copy with its own image.
     const int64_t tiles_x = (grid->nx + 7) / 8, tiles_z = (grid->nz + 7) / 8;

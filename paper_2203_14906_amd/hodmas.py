@@ -346,7 +346,7 @@ class Plan:
 
 
 class Batch:
-    """Many frames (own plan, order, storage each) in one persistent launch."""
+    """Many frames (own plan, order, storage each) in one batched launch."""
 
     def __init__(self, max_frames, max_units, max_lds_bytes=0, flags=0):
         h = ctypes.c_void_p()

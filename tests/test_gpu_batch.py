@@ -319,3 +319,27 @@ def test_mixed_orders_in_one_kernel(hd, dtype, tiling, frames):
     bt.close()
     for p in two:
         p.close()
+
+
+@pytest.mark.parametrize("extra", [0, 1, 3000])
+def test_more_units_than_the_largest_grid(hd, extra):
+    """A kind's grid ends at 65536 workgroups: units beyond it are taken by a
+    second step of the first workgroups (65536 units exactly, a few more, and
+    a part of a second round), every image bitwise its own launch."""
+    f = ph.config_frame(1)
+    arr = ph.to_fp32(f.rf)
+    rfs = [torch.from_numpy(np.ascontiguousarray(arr * s)).cuda() for s in (1.0, -0.5, 0.25)]
+    plan = hd.Plan(f.geometry, f.grid, arr.shape[1], "f32", max_order=1, tiling=(16, 8, 2, 16))
+    tiles = plan.info().n_tiles
+    n = -(-65536 // tiles) + -(-extra // tiles)
+    alone = [plan.beamform(r, 1) for r in rfs]
+    out = torch.full((n, f.grid.nz, f.grid.nx), float("nan"), dtype=torch.float32, device="cuda")
+    bt = hd.Batch(max_frames=n, max_units=n * tiles)
+    bt.set([plan] * n, [rfs[i % 3] for i in range(n)], [1] * n, list(out.unbind(0)))
+    assert bt.info().n_units == n * tiles >= 65536 + extra
+    bt.launch()
+    torch.cuda.synchronize()
+    for j in range(3):
+        assert bool((out[j::3] == alone[j]).all())
+    bt.close()
+    plan.close()
