@@ -311,22 +311,32 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     // us launched, 93 and 72 replayed), a list that barely fills the device once
     // (two paired 128 x 128 frames 23 and 12), and three or more kinds (64 such
     // frames at four orders 76 and 72, replayed 154 and 78; six at six 49 and 15)
-    // gain or lose little.
-    constexpr int64_t kShortUnit = 500000, kOneFill = 1024;   // slots; units
+    // gain or lose little.  Any number of kinds stays apart where each fills the
+    // device several times over with short units and none is paired, whose tail
+    // is then small: 128 unpaired float16 frames of 128 x 128 at four orders (8192
+    // units each) 159 us apart and 183 mixed, 384 at six 461 and 505; 64 (4096
+    // units each) 109 and 100 replayed.  Paired kernels hold the mixed kernel's
+    // six waves at the high orders, and stay mixed (384 such float32 frames 410
+    // and 393).
+    constexpr int64_t kShortUnit = 500000, kOneFill = 1024, kManyFills = 8192;   // slots; units; units
     if (comp) {
         for (int dt = 0; dt < 3; ++dt) {
             auto of_type = [&](int kind) {
                 return kind < hodmas::kOrderKinds && hodmas::kind_dtype(kind) == dt && !hodmas::kind_cf(kind);
             };
-            int present = 0;
+            int present = 0, pairing = 1;
             for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
-                present += kl[kind] != 0 && of_type(kind);
+                if (kl[kind] != 0 && of_type(kind)) {
+                    ++present;
+                    pairing = std::max(pairing, hodmas::kind_pairing(kind));
+                }
             int64_t n = 0, cost = 0;
             for (const Unit& u : units) {
                 n += of_type(u.kind);
                 cost += of_type(u.kind) ? u.cost : 0;
             }
-            if (present < 2 || (present == 2 && cost < kShortUnit * n && n > kOneFill))
+            const int64_t apart = present == 2 ? kOneFill : kManyFills * present - 1;
+            if (present < 2 || (cost < kShortUnit * n && n > apart && (present == 2 || pairing == 1)))
                 continue;
             const int mixed = hodmas::mixed_kind(dt);
             unit_cost[dt] = std::max<int64_t>(1, cost / n);

@@ -343,3 +343,33 @@ def test_more_units_than_the_largest_grid(hd, extra):
         assert bool((out[j::3] == alone[j]).all())
     bt.close()
     plan.close()
+
+
+@pytest.mark.parametrize("frames", [127, 128, 130])
+def test_long_lists_of_short_units_at_several_orders(hd, frames):
+    """Three orders whose units fill the device several times: up to 8191 units
+    an order in one kernel, from 8192 on in their own, paired ones mixed in
+    both cases; every image bitwise its own launch, launched and replayed, and
+    the list may change between the two."""
+    f = ph.make_frame(8, 300, 64, 64, n_points=5, snr_db=15.0, seed=72)
+    grid = ph.make_grid(64, 64, 8 * 0.3e-3, 9e-3)
+    rf = torch.from_numpy(ph.to_fp32(f.rf)).cuda()
+    orders = (1, 3, 6)
+    for flags in (0, hd.FLAG_MIRROR):
+        plan = hd.Plan(f.geometry, grid, 300, "f32", max_order=6, tiling=(8, 8, 4, 0), flags=flags)
+        assert plan.info().n_tiles == 64
+        own = [plan.beamform(rf, k) for k in orders]
+        out = torch.empty((3, frames, 64, 64), device="cuda")
+        bt = hd.Batch(3 * frames, 3 * frames * 64, plan.info().lds_bytes)
+        for used in (frames, 20, frames):
+            bt.set([plan] * (3 * used), [rf] * (3 * used), [k for k in orders for _ in range(used)],
+                   [out[i, j] for i in range(3) for j in range(used)])
+            bt.capture()
+            for go in (bt.launch, bt.replay, bt.replay):
+                out.fill_(float("nan"))
+                go()
+                torch.cuda.synchronize()
+                for i in range(3):
+                    assert bool((out[i, :used] == own[i]).all()), (flags, used, orders[i])
+        bt.close()
+        plan.close()
