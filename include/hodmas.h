@@ -279,8 +279,9 @@ hodmas_status hodmas_plan_tables(hodmas_plan_t plan, const hodmas_tile_desc** ti
  * captured graph holds the kernels of all kinds, so one graph launch runs the
  * whole batch.  Each tile runs exactly the per-frame code, so every
  * frame's image is bitwise the same as from hodmas_beamform with its plan,
- * whatever else is in the batch.  A batch object is used from one stream at a
- * time.
+ * whatever else is in the batch.  A batch object is used from one host thread
+ * at a time.  Launches and replays only read the work list, so those of one list
+ * may overlap, on any streams; a set must not overlap them.
  * ------------------------------------------------------------------------- */
 typedef struct hodmas_batch_s* hodmas_batch_t;
 

@@ -102,25 +102,13 @@ struct Unit {
     int32_t kind, frame, tile;
 };
 
-// Units a workgroup of a mixed kind takes per draw: one, but where units are
-// short as many as make up half a million slots, which an XCD forms in some
-// 70 ns, the time of a draw, as long as a workgroup still draws four
-// times (256 frames of 128 x 128 at four orders, 64 elements: 470 us one at a
-// time, 325 five at a time).
-int32_t draw_size(int64_t unit_cost, int64_t units, int64_t workgroups)
-{
-    constexpr int64_t kDrawCost = 500000;
-    const int64_t most = workgroups > 0 ? units / (4 * workgroups) : 1;
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>((kDrawCost + unit_cost - 1) / unit_cost, most));
-}
-
 // A mixed kind's n units, in frame and tile order, dealt to `used` XCDs: every
 // frame is cut into that many bands of tile rows of about equal estimated cost,
 // and each XCD takes one of each frame -- another one of the next, as costs
 // that the estimate misses go with depth -- so all have the same mix of orders
 // and record ends whatever those cost.  (Contiguous runs, an XCD all of a few
 // frames, as the kinds of one order are cut, rest on the estimate across orders:
-// 753 us where this takes 685, 24 frames of 17 shapes.)  cut[x] .. cut[x + 1]
+// 753 us where this took 685, 24 frames of 17 shapes.)  cut[x] .. cut[x + 1]
 // becomes XCD x's run: its bands, those of the heaviest units first.
 void deal_frames(Unit* run, int n, int used, int32_t* cut, std::vector<Unit>& dealt)
 {
@@ -160,23 +148,19 @@ void deal_frames(Unit* run, int n, int used, int32_t* cut, std::vector<Unit>& de
     std::copy(dealt.begin(), dealt.end(), run);
 }
 
-// Workgroups a kind's kernel launches with.  The kernels of one order take one
-// per unit: the device hands a workgroup out as another ends, which evens out
-// better than fixed shares of a grid that just fills the device.  Measured so,
-// and with fixed shares: one unpaired 2048 x 2048 frame from 256 elements at
-// order 1 501 and 659 us, at order 6 789 and 917; one of 512 x 512 from 128 at
-// order 2 28.8 and 39.5; eight of them at order 6, paired, 187 and 191; at order
-// 1 90 and 89; 256 of 128 x 128 at order 1 264 and 309.  From kMostWorkgroups on
-// each takes several (1100 of 128 x 128, 70400 units: 1031 and 1254 us).  A
-// mixed kind's kernel, which draws its units, runs as many workgroups as its
-// LDS lets the device hold, cut to its unit count: it evens out by drawing, and
-// starting it once per unit costs more (24 float16 frames 712 against 685 us).
+// Workgroups a kind's kernel launches with: one per unit.  The device hands a
+// workgroup out as another ends, which evens out better than fixed shares of a
+// grid that just fills the device.  Measured so, and with fixed shares: one
+// unpaired 2048 x 2048 frame from 256 elements at order 1 501 and 659 us, at
+// order 6 789 and 917; one of 512 x 512 from 128 at order 2 28.8 and 39.5; eight
+// of them at order 6, paired, 187 and 191; at order 1 90 and 89; 256 of 128 x 128
+// at order 1 264 and 309; 24 FP16 frames of 17 shapes at all orders as a mixed
+// kind 697 and 862.  From kMostWorkgroups on each takes several (1100 of 128 x
+// 128, 70400 units: 1031 and 1254 us).
 int launch_grid(const hodmas_batch_s* b, int kind)
 {
     constexpr int kMostWorkgroups = 1 << 16;
-    if (kind < hodmas::kOrderKinds)
-        return (int)std::min<int64_t>((int64_t)b->longest[kind] * hodmas::kXcds, kMostWorkgroups);
-    return (int)std::min<int64_t>(b->kind_grid[kind], b->end[kind] - b->begin[kind]);
+    return (int)std::min<int64_t>((int64_t)b->longest[kind] * hodmas::kXcds, kMostWorkgroups);
 }
 
 }  // namespace
@@ -261,7 +245,6 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     std::vector<Unit> units;
     int64_t pixch = 0;
     const bool comp = !(b->flags & HODMAS_FLAG_ACC_PLAIN);
-    int64_t unit_cost[3] = {1, 1, 1};       // a mixed kind's mean, by storage type
     int64_t kl[hodmas::kBatchKinds] = {};   // LDS each kind's largest plan needs
     try {
         for (int32_t f = 0; f < n_frames; ++f) {
@@ -339,7 +322,6 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
             if (present < 2 || (cost < kShortUnit * n && n > apart && (present == 2 || pairing == 1)))
                 continue;
             const int mixed = hodmas::mixed_kind(dt);
-            unit_cost[dt] = std::max<int64_t>(1, cost / n);
             for (Unit& u : units)
                 if (of_type(u.kind))
                     u.kind = mixed;
@@ -437,10 +419,6 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
         b->longest[k] = 0;
         for (int x = 0; x < hodmas::kXcds; ++x)
             b->longest[k] = std::max(b->longest[k], cuts[k][x + 1] - cuts[k][x]);
-    }
-    for (int dt = 0; dt < 3; ++dt) {
-        const int k = hodmas::mixed_kind(dt);
-        hdr->per_draw[dt] = draw_size(unit_cost[dt], ke[k] - kb[k], std::min<int64_t>(kg[k], ke[k] - kb[k]));
     }
     std::memcpy(b->begin, hdr->begin, sizeof(b->begin));
     std::memcpy(b->end, hdr->end, sizeof(b->end));

@@ -75,10 +75,6 @@ struct BatchHeader {
     int32_t begin[kBatchKinds];
     int32_t end[kBatchKinds];
     int32_t xcd[kBatchKinds][kXcds + 1];
-    // draws so far from each run of a mixed kind (its kernel counts; zero in a
-    // new work list and after each launch)
-    int32_t drawn[3][kXcds];
-    int32_t per_draw[3];      // units per draw of a mixed kind
 };
 
 struct BatchFrame {

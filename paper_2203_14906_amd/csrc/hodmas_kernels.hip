@@ -758,11 +758,9 @@ __device__ __forceinline__ R newton(const R (&p)[K])
 // symmetric about x = 0 (checked on the host), that pixel's delay to element
 // n-1-i equals this pixel's delay to element i, so one delay serves both and
 // the mirror pixel gathers from the mirrored rows the staging fills.
-// `staged` is called once, when the first chunk's rows are in LDS: a request to
-// memory made there is not waited for with them.
-template <int K, int DT, bool COMP, bool CF, int M, bool CHECK, int SH, class Staged>
+template <int K, int DT, bool COMP, bool CF, int M, bool CHECK, int SH>
 __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_tile_desc& td,
-                                             float* __restrict__ lds, Staged staged)
+                                             float* __restrict__ lds)
 {
     using Sums = PixelSums<K, CF, COMP>;
     constexpr bool kHalf = DT == HODMAS_F16;
@@ -784,7 +782,6 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
     };
 
     if (td.n_active < K) {
-        staged();
         // fewer contributing elements than the order: no K-subset exists, e_K = 0 exactly
         if (g == 0 && valid) {
 #pragma unroll
@@ -823,8 +820,6 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
         __syncthreads();                       // previous readers of the LDS are done
         stage_chunk<DT, M, CHECK>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
         __syncthreads();
-        if (c0 == 0)
-            staged();
         const int moff = mirror_offset(nch, td.window);  // bytes from a slot's row to its mirrored row
         const int zero = zero_offset(td.window);
         // this group's elements of the chunk: slots g, g+split, ..., stored together
@@ -884,23 +879,20 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
 // is a whole of its own: with the test inside the element loop, or with both
 // loop variants in one body, the paired kernels' sums no longer fit their
 // registers and the loop's scheduling suffers.
-struct Nothing {
-    __device__ __forceinline__ void operator()() const {}
-};
-template <int K, int DT, bool COMP, bool CF, int M, class Staged = Nothing>
-__device__ __forceinline__ void form_tile(const FrameArgs& A, int tile, float* __restrict__ lds, Staged staged = {})
+template <int K, int DT, bool COMP, bool CF, int M>
+__device__ __forceinline__ void form_tile(const FrameArgs& A, int tile, float* __restrict__ lds)
 {
     const hodmas_tile_desc td = load_const(A.tiles, tile);
     if (td.check) {
-        process_tile<K, DT, COMP, CF, M, true, 0>(A, td, lds, staged);
+        process_tile<K, DT, COMP, CF, M, true, 0>(A, td, lds);
     } else {
         if constexpr (M == 1 && !CF && K >= 2) {
             if (A.shift == 4 && td.iz0 >= A.shift_iz0) {
-                process_tile<K, DT, COMP, CF, M, false, 4>(A, td, lds, staged);
+                process_tile<K, DT, COMP, CF, M, false, 4>(A, td, lds);
                 return;
             }
         }
-        process_tile<K, DT, COMP, CF, M, false, 0>(A, td, lds, staged);
+        process_tile<K, DT, COMP, CF, M, false, 0>(A, td, lds);
     }
 }
 
@@ -942,17 +934,23 @@ __global__ __launch_bounds__(kMaxBlock) void hodmas_frame_kernel(FrameArgs A)
 // the loops, so those kernels are left at the four or five they fit.
 constexpr int batch_min_waves(int K, int M, bool CF) { return M == 2 && K == 6 && !CF ? 6 : 1; }
 
-// What the workgroups of one XCD share: its run of the kind's units.
-struct UnitRun {
-    int l, g;             // this workgroup, of so many on the XCD
-    int first, n;         // the run's units in the list
-};
-__device__ __forceinline__ UnitRun unit_run(const BatchHeader* __restrict__ hdr, int kind)
+// form(frame, tile) for each unit of this workgroup in the kind's list.
+template <class Form>
+__device__ __forceinline__ void walk_units(const BatchHeader* __restrict__ hdr, const BatchFrame* __restrict__ frames,
+                                           const BatchUnit* __restrict__ units, int kind, Form form)
 {
-    const int x = (int)blockIdx.x % kXcds;
+    const int x = (int)blockIdx.x % kXcds, l = (int)blockIdx.x / kXcds;
+    const int g = ((int)gridDim.x - x + kXcds - 1) / kXcds;   // workgroups on this XCD
     const int lo = load_const(&hdr->xcd[kind][0], x);
-    return {(int)blockIdx.x / kXcds, ((int)gridDim.x - x + kXcds - 1) / kXcds, load_const(&hdr->begin[0], kind) + lo,
-            load_const(&hdr->xcd[kind][0], x + 1) - lo};
+    const int first = load_const(&hdr->begin[0], kind) + lo;
+    const int n = load_const(&hdr->xcd[kind][0], x + 1) - lo;
+    for (int r = 0; r * g < n; ++r) {
+        const int u = (r & 1) ? (r + 1) * g - 1 - l : r * g + l;
+        if (u >= n)
+            continue;
+        const BatchUnit un = load_const(units, first + u);
+        form(load_const(frames, un.frame), un.tile);
+    }
 }
 
 template <int K, int DT, bool COMP, bool CF, int M>
@@ -961,91 +959,43 @@ void hodmas_batch_kernel(const BatchHeader* __restrict__ hdr, const BatchFrame* 
                          const BatchUnit* __restrict__ units)
 {
     extern __shared__ float lds[];
-    const UnitRun run = unit_run(hdr, batch_kind(K, DT, M, CF ? 1 : 0));
-    for (int r = 0; r * run.g < run.n; ++r) {
-        const int u = (r & 1) ? (r + 1) * run.g - 1 - run.l : r * run.g + run.l;
-        if (u >= run.n)
-            continue;
-        const BatchUnit un = load_const(units, run.first + u);
-        const BatchFrame fr = load_const(frames, un.frame);
-        form_tile<K, DT, COMP, CF, M>(fr.args, un.tile, lds);
-    }
+    walk_units(hdr, frames, units, batch_kind(K, DT, M, CF ? 1 : 0),
+               [&](const BatchFrame& fr, int tile) { form_tile<K, DT, COMP, CF, M>(fr.args, tile, lds); });
 }
 
 // Units of any order and pairing, each formed by the code of its own kind in
 // the registers of the largest (six waves, as the paired order 6 asks for), so
 // that one launch, and one tail, serves a work list whose kinds would each
-// leave the device half empty.  Their times differ too much for a fixed share
-// each: a workgroup takes the units l and 2g - 1 - l of its XCD's run (heaviest
-// first), and draws later ones, `per` at a time, each time while it forms the
-// last one in hand.  An addition to one word takes some 70 ns of the XCD's
-// workgroups' common time, hence two units without and, where units are short,
-// several per draw (draw_size on the host).  The workgroups draw until they
-// fail, one failure each, and whoever makes the last draw sets the count back
-// to zero.  The number passes through the first word of the LDS, which is free
-// between units.  Measured, FP16 mirror pairs: 24 frames of 17 shapes at all
-// orders 902 us as one kernel per kind in a graph, 889 as one kernel with fixed
-// shares, 756 with drawn units, 685 with frames dealt over the XCDs
-// (deal_frames); 16 frames set and launched 475, 349, 302 and 242 us.  In the
-// kernels of one kind, whose units are alike, drawing cost 3 % more than it
-// evened out.
+// leave the device half empty.  A workgroup per unit, as in the kernels of one
+// kind: units of different orders differ too much for equal shares of a grid
+// that fills the device (24 FP16 frames of 17 shapes, mirror pairs: 862 us so,
+// 697 with a workgroup per unit).  Like those kernels it only reads the work
+// list, so launches of one list may overlap on any streams.  (Drawing units from
+// a counter took 680 us there, but a list then belonged to one launch at a time,
+// and lists of short units waited for the counters: 18 frames of 128 x 128 at six
+// orders 50 us, 29 so.)
 template <int DT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6)))
 void hodmas_mixed_kernel(const BatchHeader* __restrict__ hdr, const BatchFrame* __restrict__ frames,
                          const BatchUnit* __restrict__ units)
 {
     extern __shared__ float lds[];
-    const UnitRun run = unit_run(hdr, mixed_kind(DT));
-    int* const counter = const_cast<int*>(&hdr->drawn[DT][blockIdx.x % kXcds]);
-    int* const number = reinterpret_cast<int*>(lds);
-    const int per = load_const(&hdr->per_draw[0], DT), third = 2 * run.g;
-    const int draws = (run.n - third + per - 1) / per + run.g;   // of all the run's workgroups
-    bool second = false;
-    for (int u = run.l, end = 0; u < run.n;) {
-        const bool draw_now = second && u + 1 >= end && run.n > third;
-        int drawn = 0;
-        auto draw = [&] {
-            if (draw_now && threadIdx.x == 0)
-                drawn = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
-        const BatchUnit un = load_const(units, run.first + u);
-        const BatchFrame fr = load_const(frames, un.frame);
-        const int tile = un.tile;
+    walk_units(hdr, frames, units, mixed_kind(DT), [&](const BatchFrame& fr, int tile) {
         switch (2 * fr.order + fr.pairing) {
-        case 3: form_tile<1, DT, true, false, 1>(fr.args, tile, lds, draw); break;
-        case 4: form_tile<1, DT, true, false, 2>(fr.args, tile, lds, draw); break;
-        case 5: form_tile<2, DT, true, false, 1>(fr.args, tile, lds, draw); break;
-        case 6: form_tile<2, DT, true, false, 2>(fr.args, tile, lds, draw); break;
-        case 7: form_tile<3, DT, true, false, 1>(fr.args, tile, lds, draw); break;
-        case 8: form_tile<3, DT, true, false, 2>(fr.args, tile, lds, draw); break;
-        case 9: form_tile<4, DT, true, false, 1>(fr.args, tile, lds, draw); break;
-        case 10: form_tile<4, DT, true, false, 2>(fr.args, tile, lds, draw); break;
-        case 11: form_tile<5, DT, true, false, 1>(fr.args, tile, lds, draw); break;
-        case 12: form_tile<5, DT, true, false, 2>(fr.args, tile, lds, draw); break;
-        case 13: form_tile<6, DT, true, false, 1>(fr.args, tile, lds, draw); break;
-        case 14: form_tile<6, DT, true, false, 2>(fr.args, tile, lds, draw); break;
+        case 3: form_tile<1, DT, true, false, 1>(fr.args, tile, lds); break;
+        case 4: form_tile<1, DT, true, false, 2>(fr.args, tile, lds); break;
+        case 5: form_tile<2, DT, true, false, 1>(fr.args, tile, lds); break;
+        case 6: form_tile<2, DT, true, false, 2>(fr.args, tile, lds); break;
+        case 7: form_tile<3, DT, true, false, 1>(fr.args, tile, lds); break;
+        case 8: form_tile<3, DT, true, false, 2>(fr.args, tile, lds); break;
+        case 9: form_tile<4, DT, true, false, 1>(fr.args, tile, lds); break;
+        case 10: form_tile<4, DT, true, false, 2>(fr.args, tile, lds); break;
+        case 11: form_tile<5, DT, true, false, 1>(fr.args, tile, lds); break;
+        case 12: form_tile<5, DT, true, false, 2>(fr.args, tile, lds); break;
+        case 13: form_tile<6, DT, true, false, 1>(fr.args, tile, lds); break;
+        case 14: form_tile<6, DT, true, false, 2>(fr.args, tile, lds); break;
         }
-        if (!second) {
-            second = true;
-            u = third - 1 - run.l;
-            end = u + 1;
-            continue;
-        }
-        if (++u < end)
-            continue;
-        if (run.n <= third)
-            break;
-        __syncthreads();                   // the unit's readers of the LDS are done
-        if (threadIdx.x == 0) {
-            *number = drawn;
-            if (drawn == draws - 1)
-                __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        u = third + __builtin_amdgcn_readfirstlane(*number) * per;
-        end = min(u + per, run.n);
-        __syncthreads();                   // and the number is read
-    }
+    });
 }
 
 // ---------------------------------------------------------------------------

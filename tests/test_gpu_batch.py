@@ -373,3 +373,44 @@ def test_long_lists_of_short_units_at_several_orders(hd, frames):
                     assert bool((out[i, :used] == own[i]).all()), (flags, used, orders[i])
         bt.close()
         plan.close()
+
+
+def test_launches_of_one_list_overlap_on_several_streams(hd):
+    """Launches and replays of one list of several orders, each on its own
+    stream and none waiting for another, between products that leave them a part
+    of the device; then launches and replays alone: every one forms every unit
+    (a launch only reads the list)."""
+    f = ph.config_frame(1)
+    arr = ph.to_fp32(f.rf)
+    rf = torch.from_numpy(arr).cuda()
+    plan = hd.Plan(f.geometry, f.grid, arr.shape[1], "f32", max_order=6, tiling=(16, 16, 1, 16), flags=hd.FLAG_MIRROR)
+    own = {k: plan.beamform(rf, k).clone() for k in range(1, 7)}
+    orders = [i % 6 + 1 for i in range(240)]
+    outs = [torch.empty((f.grid.nz, f.grid.nx), device="cuda") for _ in orders]
+    bt = hd.Batch(len(orders), len(orders) * plan.info().n_tiles, plan.info().lds_bytes)
+    bt.set([plan] * len(orders), [rf] * len(orders), orders, outs)
+    bt.capture()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    busy = torch.randn((4096, 4096), device="cuda")
+
+    def check(what, *runs):
+        for o in outs:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for go, stream in runs:
+            go(stream=stream)
+        torch.cuda.synchronize()
+        for i, (o, k) in enumerate(zip(outs, orders)):
+            assert torch.equal(o, own[k]), (what, i)
+
+    for rep in range(4):
+        say("overlapping launches, round %d" % rep)
+        torch.cuda.synchronize()
+        busy @ busy
+        for i in range(6):
+            (bt.replay if i == 3 else bt.launch)(stream=streams[i % 3])
+        torch.cuda.synchronize()
+        check("launch", (bt.launch, streams[0]))
+        check("replay", (bt.replay, streams[1]))
+    bt.close()
+    plan.close()
