@@ -16,6 +16,7 @@
 using hodmas::BatchFrame;
 using hodmas::BatchHeader;
 using hodmas::BatchUnit;
+using hodmas::DrawCount;
 
 namespace {
 
@@ -25,6 +26,7 @@ constexpr size_t kAlign = 256;
 // only used to order the work list, heaviest units first.
 constexpr int64_t kSlots[7] = {0, 19, 25, 32, 32, 36, 38};
 constexpr int64_t kCfSlots = 4;   // coherence weighting: two more compensated sums
+constexpr int kLaunches = 4;      // direct launches of one list with draw counts of their own
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -47,7 +49,8 @@ struct hodmas_batch_s {
     // the last occupancy answer per kind (a serving loop sets a list per launch)
     int64_t occ_lds[hodmas::kBatchKinds] = {};
     int occ_per_cu[hodmas::kBatchKinds] = {};
-    size_t off_frames = 0, off_units = 0, bytes = 0;
+    bool draws[3] = {};                   // by storage type: the list's mixed kind draws its units
+    size_t off_frames = 0, off_units = 0, off_counts = 0, bytes = 0;
     char* d_buf = nullptr;
     char* h_buf = nullptr;           // pinned staging of the work list
     hipEvent_t copied = nullptr;     // last host->device copy of h_buf
@@ -60,9 +63,17 @@ struct hodmas_batch_s {
     int node_grid[hodmas::kBatchKinds] = {};         // its current grid in `exec`
     int64_t node_lds[hodmas::kBatchKinds] = {};      // and its dynamic LDS
     bool node_on[hodmas::kBatchKinds] = {};          // enabled in `exec`
-    hipEvent_t replayed = nullptr;   // the last replay's completion
-    bool replay_pending = false;
-    hipEvent_t launched = nullptr;   // the last direct launch's completion (destroy waits for it)
+    bool node_draws[hodmas::kBatchKinds] = {};       // with the graph's draw counts
+    // Draw counts belong to one launch at a time: set 0 to the graph, set 1 + i
+    // to the direct launches that take runs[i] in turn.  A launch on another
+    // stream than the one before it with the same set waits for that one's end.
+    struct Run {
+        hipEvent_t done = nullptr;   // destroy waits for it
+        hipStream_t stream = nullptr;
+        bool pending = false;
+    };
+    Run replayed, runs[kLaunches];
+    int next_run = 0;
     hodmas_batch_info info{};
 };
 
@@ -70,14 +81,13 @@ namespace {
 
 void release(hodmas_batch_s* b)
 {
-    if (b->launched) {
-        (void)hipEventSynchronize(b->launched);
-        (void)hipEventDestroy(b->launched);
-        b->launched = nullptr;
-    }
-    if (b->replayed) {
-        (void)hipEventSynchronize(b->replayed);
-        (void)hipEventDestroy(b->replayed);
+    for (hodmas_batch_s::Run* r : {&b->replayed, &b->runs[0], &b->runs[1], &b->runs[2], &b->runs[3]}) {
+        static_assert(kLaunches == 4, "every run");
+        if (r->done) {
+            (void)hipEventSynchronize(r->done);
+            (void)hipEventDestroy(r->done);
+            r->done = nullptr;
+        }
     }
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
@@ -89,7 +99,6 @@ void release(hodmas_batch_s* b)
     if (b->h_buf) (void)hipHostFree(b->h_buf);
     b->exec = nullptr;
     b->graph = nullptr;
-    b->replayed = nullptr;
     b->copied = nullptr;
     b->d_buf = nullptr;
     b->h_buf = nullptr;
@@ -154,13 +163,53 @@ void deal_frames(Unit* run, int n, int used, int32_t* cut, std::vector<Unit>& de
 // unpaired 2048 x 2048 frame from 256 elements at order 1 501 and 659 us, at
 // order 6 789 and 917; one of 512 x 512 from 128 at order 2 28.8 and 39.5; eight
 // of them at order 6, paired, 187 and 191; at order 1 90 and 89; 256 of 128 x 128
-// at order 1 264 and 309; 24 FP16 frames of 17 shapes at all orders as a mixed
-// kind 697 and 862.  From kMostWorkgroups on each takes several (1100 of 128 x
-// 128, 70400 units: 1031 and 1254 us).
-int launch_grid(const hodmas_batch_s* b, int kind)
+// at order 1 264 and 309.  From kMostWorkgroups on each takes several (1100 of 128 x
+// 128, 70400 units: 1031 and 1254 us).  A mixed kind that fills the device twice
+// draws its units instead, with as many workgroups as the device holds, which
+// saves the start of a workgroup for each (24 FP16 frames of 17 shapes at all
+// orders 862 us with fixed shares, 697 one per unit, 679 drawn).
+int launch_grid(const hodmas_batch_s* b, int kind, bool draws)
 {
     constexpr int kMostWorkgroups = 1 << 16;
+    if (draws)
+        return b->kind_grid[kind];
     return (int)std::min<int64_t>((int64_t)b->longest[kind] * hodmas::kXcds, kMostWorkgroups);
+}
+
+bool kind_draws(const hodmas_batch_s* b, int kind)
+{
+    return kind >= hodmas::kOrderKinds && b->draws[kind - hodmas::kOrderKinds];
+}
+
+// What the batch kernels take.
+struct KernelArgs {
+    const BatchHeader* hdr;
+    const BatchFrame* frames;
+    const BatchUnit* units;
+    DrawCount* counts;
+    void* ptr[4] = {&hdr, &frames, &units, &counts};
+    // counts: the set the launch draws with, or -1
+    KernelArgs(const hodmas_batch_s* b, int set)
+        : hdr(reinterpret_cast<const BatchHeader*>(b->d_buf)),
+          frames(reinterpret_cast<const BatchFrame*>(b->d_buf + b->off_frames)),
+          units(reinterpret_cast<const BatchUnit*>(b->d_buf + b->off_units)),
+          counts(set < 0 ? nullptr
+                         : reinterpret_cast<DrawCount*>(b->d_buf + b->off_counts) + set * hodmas::kDrawCounts)
+    {
+    }
+    KernelArgs(const KernelArgs&) = delete;
+};
+
+// Puts work on `st` behind the run's last, if that was on another stream.
+bool follow(const hodmas_batch_s::Run& run, hipStream_t st)
+{
+    return !run.pending || run.stream == st || hipStreamWaitEvent(st, run.done, 0) == hipSuccess;
+}
+bool finish(hodmas_batch_s::Run& run, hipStream_t st)
+{
+    run.stream = st;
+    run.pending = hipEventRecord(run.done, st) == hipSuccess;
+    return run.pending;
 }
 
 }  // namespace
@@ -213,11 +262,14 @@ hodmas_status hodmas_batch_create(int32_t max_frames, int64_t max_units, int64_t
     b->cus = prop.multiProcessorCount;
     b->off_frames = align_up(sizeof(BatchHeader));
     b->off_units = b->off_frames + align_up(sizeof(BatchFrame) * (size_t)max_frames);
-    b->bytes = b->off_units + align_up(sizeof(BatchUnit) * (size_t)max_units);
-    if (hipMalloc((void**)&b->d_buf, b->bytes) != hipSuccess ||
-        hipHostMalloc((void**)&b->h_buf, b->bytes, hipHostMallocDefault) != hipSuccess ||
-        hipEventCreateWithFlags(&b->copied, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&b->launched, hipEventDisableTiming) != hipSuccess) {
+    b->off_counts = b->off_units + align_up(sizeof(BatchUnit) * (size_t)max_units);
+    b->bytes = b->off_counts + sizeof(DrawCount) * hodmas::kDrawCounts * (1 + kLaunches);
+    bool ok = hipMalloc((void**)&b->d_buf, b->bytes) == hipSuccess &&
+              hipHostMalloc((void**)&b->h_buf, b->bytes, hipHostMallocDefault) == hipSuccess &&
+              hipEventCreateWithFlags(&b->copied, hipEventDisableTiming) == hipSuccess;
+    for (hodmas_batch_s::Run& r : b->runs)
+        ok = ok && hipEventCreateWithFlags(&r.done, hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
         (void)hipGetLastError();
         release(b);
         delete b;
@@ -420,6 +472,10 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
         for (int x = 0; x < hodmas::kXcds; ++x)
             b->longest[k] = std::max(b->longest[k], cuts[k][x + 1] - cuts[k][x]);
     }
+    for (int dt = 0; dt < 3; ++dt) {
+        const int k = hodmas::mixed_kind(dt);
+        b->draws[dt] = ke[k] - kb[k] > 2 * kg[k];   // two units without drawing
+    }
     std::memcpy(b->begin, hdr->begin, sizeof(b->begin));
     std::memcpy(b->end, hdr->end, sizeof(b->end));
     std::memcpy(b->kind_lds, kl, sizeof(kl));
@@ -454,20 +510,33 @@ hodmas_status hodmas_batch_launch(hodmas_batch_t b, void* stream)
 {
     if (!valid_batch(b) || !b->has_list)
         return HODMAS_EINVAL;
-    const BatchHeader* hdr = reinterpret_cast<const BatchHeader*>(b->d_buf);
-    const BatchFrame* frames = reinterpret_cast<const BatchFrame*>(b->d_buf + b->off_frames);
-    const BatchUnit* units = reinterpret_cast<const BatchUnit*>(b->d_buf + b->off_units);
-    const bool comp = !(b->flags & HODMAS_FLAG_ACC_PLAIN);
-    for (int kind = 0; kind < hodmas::kBatchKinds; ++kind) {
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    // A captured launch may run again at any time beside others, so it gets no
+    // draw counts (and the event would be the capture's, not this launch's).
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool captured = hipStreamIsCapturing(st, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+    const int turn = b->next_run;
+    hodmas_batch_s::Run& run = b->runs[turn];
+    KernelArgs drawing(b, 1 + turn), fixed(b, -1);
+    bool ok = true;
+    for (int kind = 0; kind < hodmas::kBatchKinds && ok; ++kind) {
         if (b->end[kind] <= b->begin[kind])
             continue;
-        if (hodmas::launch_batch(kind, hdr, frames, units, launch_grid(b, kind), comp, b->kind_lds[kind], stream) !=
-            0) {
-            (void)hipGetLastError();
-            return HODMAS_EDEVICE;
-        }
+        const bool draws = !captured && kind_draws(b, kind);
+        const int grid = launch_grid(b, kind, draws);
+        if (kind < hodmas::kOrderKinds)
+            ok = hodmas::launch_batch(kind, fixed.hdr, fixed.frames, fixed.units, grid,
+                                      !(b->flags & HODMAS_FLAG_ACC_PLAIN), b->kind_lds[kind], stream) == 0;
+        else
+            ok = (!draws || follow(run, st)) &&
+                 hipLaunchKernel(hodmas::batch_kernel(kind, true), dim3(grid), dim3(hodmas::kBlock),
+                                 (draws ? drawing : fixed).ptr, (size_t)b->kind_lds[kind], st) == hipSuccess;
     }
-    if (hipEventRecord(b->launched, static_cast<hipStream_t>(stream)) != hipSuccess) {
+    if (!captured) {
+        ok = finish(run, st) && ok;
+        b->next_run = (turn + 1) % kLaunches;
+    }
+    if (!ok) {
         (void)hipGetLastError();
         return HODMAS_EDEVICE;
     }
@@ -490,7 +559,7 @@ hodmas_status hodmas_batch_launch(hodmas_batch_t b, void* stream)
 // (launch_grid).
 namespace {
 
-hipKernelNodeParams node_params(const hodmas_batch_s* b, int kind, int grid, int64_t lds, void** args)
+hipKernelNodeParams node_params(const hodmas_batch_s* b, int kind, int grid, int64_t lds, KernelArgs& args)
 {
     hipKernelNodeParams kp;
     std::memset(&kp, 0, sizeof(kp));
@@ -498,7 +567,7 @@ hipKernelNodeParams node_params(const hodmas_batch_s* b, int kind, int grid, int
     kp.gridDim = dim3(grid);
     kp.blockDim = dim3(hodmas::kBlock);
     kp.sharedMemBytes = (unsigned)lds;
-    kp.kernelParams = args;
+    kp.kernelParams = args.ptr;
     kp.extra = nullptr;
     return kp;
 }
@@ -510,10 +579,7 @@ bool build_graph(hodmas_batch_s* b, const bool* want)
     if (b->graph) (void)hipGraphDestroy(b->graph);
     b->exec = nullptr;
     b->graph = nullptr;
-    const BatchHeader* hdr = reinterpret_cast<const BatchHeader*>(b->d_buf);
-    const BatchFrame* frames = reinterpret_cast<const BatchFrame*>(b->d_buf + b->off_frames);
-    const BatchUnit* units = reinterpret_cast<const BatchUnit*>(b->d_buf + b->off_units);
-    void* args[] = {(void*)&hdr, (void*)&frames, (void*)&units};
+    KernelArgs args(b, -1);
     bool ok = hipGraphCreate(&b->graph, 0) == hipSuccess;
     for (int kind = 0; kind < hodmas::kBatchKinds && ok; ++kind) {
         b->node[kind] = nullptr;
@@ -527,11 +593,12 @@ bool build_graph(hodmas_batch_s* b, const bool* want)
         b->node_grid[kind] = b->grid[kind];
         b->node_lds[kind] = b->lds_bytes;
         b->node_on[kind] = true;
+        b->node_draws[kind] = false;
     }
     if (ok)
         ok = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0) == hipSuccess;
-    if (ok && !b->replayed)
-        ok = hipEventCreateWithFlags(&b->replayed, hipEventDisableTiming) == hipSuccess;
+    if (ok && !b->replayed.done)
+        ok = hipEventCreateWithFlags(&b->replayed.done, hipEventDisableTiming) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         if (b->exec) (void)hipGraphExecDestroy(b->exec);
@@ -565,25 +632,22 @@ hodmas_status hodmas_batch_replay(hodmas_batch_t b, void* stream)
 {
     if (!valid_batch(b) || !b->exec || !b->has_list)
         return HODMAS_EINVAL;
-    const BatchHeader* hdr = reinterpret_cast<const BatchHeader*>(b->d_buf);
-    const BatchFrame* frames = reinterpret_cast<const BatchFrame*>(b->d_buf + b->off_frames);
-    const BatchUnit* units = reinterpret_cast<const BatchUnit*>(b->d_buf + b->off_units);
-    void* args[] = {(void*)&hdr, (void*)&frames, (void*)&units};
+    hipStream_t st = static_cast<hipStream_t>(stream);
     // a launch of `exec` still in flight must not see its nodes change
     bool change = false, missing = false;
     for (int kind = 0; kind < hodmas::kBatchKinds; ++kind) {
         const int n = b->end[kind] - b->begin[kind];
         missing = missing || (n > 0 && !b->node[kind]);
         change = change || (n > 0) != b->node_on[kind] ||
-                 (n > 0 && (launch_grid(b, kind) != b->node_grid[kind] ||
-                            b->kind_lds[kind] != b->node_lds[kind]));
+                 (n > 0 && (launch_grid(b, kind, kind_draws(b, kind)) != b->node_grid[kind] ||
+                            kind_draws(b, kind) != b->node_draws[kind] || b->kind_lds[kind] != b->node_lds[kind]));
     }
-    if ((change || missing) && b->replay_pending) {
-        if (hipEventSynchronize(b->replayed) != hipSuccess) {
+    if ((change || missing) && b->replayed.pending) {
+        if (hipEventSynchronize(b->replayed.done) != hipSuccess) {
             (void)hipGetLastError();
             return HODMAS_EDEVICE;
         }
-        b->replay_pending = false;
+        b->replayed.pending = false;
     }
     if (missing) {
         // a kind the graph has no node for: rebuild with every kind seen so far
@@ -600,14 +664,18 @@ hodmas_status hodmas_batch_replay(hodmas_batch_t b, void* stream)
         const int n = b->end[kind] - b->begin[kind];
         const bool on = n > 0;
         if (on) {
-            const int grid = launch_grid(b, kind);
-            if (grid != b->node_grid[kind] || b->kind_lds[kind] != b->node_lds[kind]) {
+            const bool draws = kind_draws(b, kind);
+            const int grid = launch_grid(b, kind, draws);
+            if (grid != b->node_grid[kind] || draws != b->node_draws[kind] ||
+                b->kind_lds[kind] != b->node_lds[kind]) {
+                KernelArgs args(b, draws ? 0 : -1);
                 const hipKernelNodeParams kp = node_params(b, kind, grid, b->kind_lds[kind], args);
                 if (hipGraphExecKernelNodeSetParams(b->exec, b->node[kind], &kp) != hipSuccess) {
                     (void)hipGetLastError();
                     return HODMAS_EDEVICE;
                 }
                 b->node_grid[kind] = grid;
+                b->node_draws[kind] = draws;
                 b->node_lds[kind] = b->kind_lds[kind];
             }
         }
@@ -619,12 +687,11 @@ hodmas_status hodmas_batch_replay(hodmas_batch_t b, void* stream)
             b->node_on[kind] = on;
         }
     }
-    if (hipGraphLaunch(b->exec, static_cast<hipStream_t>(stream)) != hipSuccess ||
-        hipEventRecord(b->replayed, static_cast<hipStream_t>(stream)) != hipSuccess) {
+    const bool ok = follow(b->replayed, st) && hipGraphLaunch(b->exec, st) == hipSuccess;
+    if (!(finish(b->replayed, st) && ok)) {
         (void)hipGetLastError();
         return HODMAS_EDEVICE;
     }
-    b->replay_pending = true;
     return HODMAS_OK;
 }
 

@@ -91,6 +91,14 @@ struct BatchUnit {
     int32_t tile;
 };
 
+// Units that the workgroups of one XCD have drawn from its run of a mixed kind,
+// in a line of its own; zero before and after each launch.  A launch that draws
+// has [3][kXcds] of them to itself.
+struct alignas(128) DrawCount {
+    int32_t n;
+};
+constexpr int kDrawCounts = 3 * kXcds;
+
 // Launch one frame on `stream`.  Returns hipSuccess or the launch error code.
 // mirror: pair each tile of the grid's left half with its mirror image (grid
 // n_tiles / 2); the plan has checked that the geometry allows it.
@@ -145,9 +153,10 @@ FrameArgs frame_args(const hodmas_plan_s* plan, const void* rf_dev, float* image
 int launch_orders(const FrameArgs& a, const OrderImages& out, int kmax, int dtype, bool compensated,
                   int64_t lds_bytes, void* stream);
 
-// The batched kernel of one kind (for graph nodes) and a launch of
-// it.  Coherence-weighted kinds exist for compensated accumulation only
-// (batch_kernel returns null for the others).
+// The batched kernel of one kind, whose arguments are the header, the frames
+// and the units -- a mixed kind's kernel takes a DrawCount* after them, or null --
+// and a launch of a kind of one order.  Coherence-weighted and mixed kinds exist
+// for compensated accumulation only (batch_kernel returns null for the others).
 const void* batch_kernel(int kind, bool compensated);
 int launch_batch(int kind, const BatchHeader* hdr, const BatchFrame* frames, const BatchUnit* units, int grid,
                  bool compensated, int64_t lds_bytes, void* stream);

@@ -758,9 +758,11 @@ __device__ __forceinline__ R newton(const R (&p)[K])
 // symmetric about x = 0 (checked on the host), that pixel's delay to element
 // n-1-i equals this pixel's delay to element i, so one delay serves both and
 // the mirror pixel gathers from the mirrored rows the staging fills.
-template <int K, int DT, bool COMP, bool CF, int M, bool CHECK, int SH>
+// `staged` is called once, when the first chunk's rows are in LDS: a request to
+// memory made there is not waited for with them.
+template <int K, int DT, bool COMP, bool CF, int M, bool CHECK, int SH, class Staged>
 __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_tile_desc& td,
-                                             float* __restrict__ lds)
+                                             float* __restrict__ lds, Staged staged)
 {
     using Sums = PixelSums<K, CF, COMP>;
     constexpr bool kHalf = DT == HODMAS_F16;
@@ -782,6 +784,7 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
     };
 
     if (td.n_active < K) {
+        staged();
         // fewer contributing elements than the order: no K-subset exists, e_K = 0 exactly
         if (g == 0 && valid) {
 #pragma unroll
@@ -820,6 +823,8 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
         __syncthreads();                       // previous readers of the LDS are done
         stage_chunk<DT, M, CHECK>(A, St + c0, nch, td.window, lds, wave, nwaves, lane);
         __syncthreads();
+        if (c0 == 0)
+            staged();
         const int moff = mirror_offset(nch, td.window);  // bytes from a slot's row to its mirrored row
         const int zero = zero_offset(td.window);
         // this group's elements of the chunk: slots g, g+split, ..., stored together
@@ -879,20 +884,23 @@ __device__ __forceinline__ void process_tile(const FrameArgs& A, const hodmas_ti
 // is a whole of its own: with the test inside the element loop, or with both
 // loop variants in one body, the paired kernels' sums no longer fit their
 // registers and the loop's scheduling suffers.
-template <int K, int DT, bool COMP, bool CF, int M>
-__device__ __forceinline__ void form_tile(const FrameArgs& A, int tile, float* __restrict__ lds)
+struct Nothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int K, int DT, bool COMP, bool CF, int M, class Staged = Nothing>
+__device__ __forceinline__ void form_tile(const FrameArgs& A, int tile, float* __restrict__ lds, Staged staged = {})
 {
     const hodmas_tile_desc td = load_const(A.tiles, tile);
     if (td.check) {
-        process_tile<K, DT, COMP, CF, M, true, 0>(A, td, lds);
+        process_tile<K, DT, COMP, CF, M, true, 0>(A, td, lds, staged);
     } else {
         if constexpr (M == 1 && !CF && K >= 2) {
             if (A.shift == 4 && td.iz0 >= A.shift_iz0) {
-                process_tile<K, DT, COMP, CF, M, false, 4>(A, td, lds);
+                process_tile<K, DT, COMP, CF, M, false, 4>(A, td, lds, staged);
                 return;
             }
         }
-        process_tile<K, DT, COMP, CF, M, false, 0>(A, td, lds);
+        process_tile<K, DT, COMP, CF, M, false, 0>(A, td, lds, staged);
     }
 }
 
@@ -934,23 +942,19 @@ __global__ __launch_bounds__(kMaxBlock) void hodmas_frame_kernel(FrameArgs A)
 // the loops, so those kernels are left at the four or five they fit.
 constexpr int batch_min_waves(int K, int M, bool CF) { return M == 2 && K == 6 && !CF ? 6 : 1; }
 
-// form(frame, tile) for each unit of this workgroup in the kind's list.
-template <class Form>
-__device__ __forceinline__ void walk_units(const BatchHeader* __restrict__ hdr, const BatchFrame* __restrict__ frames,
-                                           const BatchUnit* __restrict__ units, int kind, Form form)
+// This workgroup among those of one XCD, and the XCD's run of the kind's units.
+struct UnitRun {
+    int l, g;             // this workgroup, of so many on the XCD
+    int first, n;         // the run's units in the list
+    // the workgroup's unit of round r, below n while it has one
+    __device__ __forceinline__ int unit(int r) const { return (r & 1) ? (r + 1) * g - 1 - l : r * g + l; }
+};
+__device__ __forceinline__ UnitRun unit_run(const BatchHeader* __restrict__ hdr, int kind)
 {
-    const int x = (int)blockIdx.x % kXcds, l = (int)blockIdx.x / kXcds;
-    const int g = ((int)gridDim.x - x + kXcds - 1) / kXcds;   // workgroups on this XCD
+    const int x = (int)blockIdx.x % kXcds;
     const int lo = load_const(&hdr->xcd[kind][0], x);
-    const int first = load_const(&hdr->begin[0], kind) + lo;
-    const int n = load_const(&hdr->xcd[kind][0], x + 1) - lo;
-    for (int r = 0; r * g < n; ++r) {
-        const int u = (r & 1) ? (r + 1) * g - 1 - l : r * g + l;
-        if (u >= n)
-            continue;
-        const BatchUnit un = load_const(units, first + u);
-        form(load_const(frames, un.frame), un.tile);
-    }
+    return {(int)blockIdx.x / kXcds, ((int)gridDim.x - x + kXcds - 1) / kXcds, load_const(&hdr->begin[0], kind) + lo,
+            load_const(&hdr->xcd[kind][0], x + 1) - lo};
 }
 
 template <int K, int DT, bool COMP, bool CF, int M>
@@ -959,43 +963,76 @@ void hodmas_batch_kernel(const BatchHeader* __restrict__ hdr, const BatchFrame* 
                          const BatchUnit* __restrict__ units)
 {
     extern __shared__ float lds[];
-    walk_units(hdr, frames, units, batch_kind(K, DT, M, CF ? 1 : 0),
-               [&](const BatchFrame& fr, int tile) { form_tile<K, DT, COMP, CF, M>(fr.args, tile, lds); });
+    const UnitRun run = unit_run(hdr, batch_kind(K, DT, M, CF ? 1 : 0));
+    for (int r = 0, u = run.l; u < run.n; u = run.unit(++r)) {
+        const BatchUnit un = load_const(units, run.first + u);
+        const BatchFrame fr = load_const(frames, un.frame);
+        form_tile<K, DT, COMP, CF, M>(fr.args, un.tile, lds);
+    }
 }
 
 // Units of any order and pairing, each formed by the code of its own kind in
 // the registers of the largest (six waves, as the paired order 6 asks for), so
 // that one launch, and one tail, serves a work list whose kinds would each
-// leave the device half empty.  A workgroup per unit, as in the kernels of one
-// kind: units of different orders differ too much for equal shares of a grid
-// that fills the device (24 FP16 frames of 17 shapes, mirror pairs: 862 us so,
-// 697 with a workgroup per unit).  Like those kernels it only reads the work
-// list, so launches of one list may overlap on any streams.  (Drawing units from
-// a counter took 680 us there, but a list then belonged to one launch at a time,
-// and lists of short units waited for the counters: 18 frames of 128 x 128 at six
-// orders 50 us, 29 so.)
+// leave the device half empty.  Units of several orders differ too much for equal
+// shares of a grid that fills the device (24 FP16 frames of 17 shapes, mirror
+// pairs: 862 us).  Without counts (null) the grid has a workgroup per unit (697 us).
+// With them it fills the device and workgroups draw: after units l and 2g - 1 - l
+// of its XCD's run (heaviest first) a workgroup asks for its next one while it
+// forms the last in hand (679 us).  counts belongs to this launch alone until it
+// ends, so launches of one list may overlap.  The workgroups of a run draw until
+// they fail, one failure each, and whoever makes the last draw sets the count back
+// to zero.  Counts of different XCDs stand in lines of their own: in one line, the
+// draws of all XCDs waited for each other (36 frames of 128 x 128 at six orders 103
+// us, 54 apart).  The number passes through the first word of the LDS, which is
+// free between units.
 template <int DT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6)))
 void hodmas_mixed_kernel(const BatchHeader* __restrict__ hdr, const BatchFrame* __restrict__ frames,
-                         const BatchUnit* __restrict__ units)
+                         const BatchUnit* __restrict__ units, DrawCount* counts)
 {
     extern __shared__ float lds[];
-    walk_units(hdr, frames, units, mixed_kind(DT), [&](const BatchFrame& fr, int tile) {
+    const UnitRun run = unit_run(hdr, mixed_kind(DT));
+    const int fixed = 2 * run.g;                     // units taken without drawing
+    const bool draws = counts != nullptr && run.n > fixed;
+    int* const count = &counts[DT * kXcds + blockIdx.x % kXcds].n;
+    int* const number = reinterpret_cast<int*>(lds);
+    for (int r = 0, u = run.l; u < run.n;) {
+        int drawn = 0;
+        auto draw = [&] {
+            if (draws && r > 0 && threadIdx.x == 0)
+                drawn = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        const BatchUnit un = load_const(units, run.first + u);
+        const BatchFrame fr = load_const(frames, un.frame);
         switch (2 * fr.order + fr.pairing) {
-        case 3: form_tile<1, DT, true, false, 1>(fr.args, tile, lds); break;
-        case 4: form_tile<1, DT, true, false, 2>(fr.args, tile, lds); break;
-        case 5: form_tile<2, DT, true, false, 1>(fr.args, tile, lds); break;
-        case 6: form_tile<2, DT, true, false, 2>(fr.args, tile, lds); break;
-        case 7: form_tile<3, DT, true, false, 1>(fr.args, tile, lds); break;
-        case 8: form_tile<3, DT, true, false, 2>(fr.args, tile, lds); break;
-        case 9: form_tile<4, DT, true, false, 1>(fr.args, tile, lds); break;
-        case 10: form_tile<4, DT, true, false, 2>(fr.args, tile, lds); break;
-        case 11: form_tile<5, DT, true, false, 1>(fr.args, tile, lds); break;
-        case 12: form_tile<5, DT, true, false, 2>(fr.args, tile, lds); break;
-        case 13: form_tile<6, DT, true, false, 1>(fr.args, tile, lds); break;
-        case 14: form_tile<6, DT, true, false, 2>(fr.args, tile, lds); break;
+        case 3: form_tile<1, DT, true, false, 1>(fr.args, un.tile, lds, draw); break;
+        case 4: form_tile<1, DT, true, false, 2>(fr.args, un.tile, lds, draw); break;
+        case 5: form_tile<2, DT, true, false, 1>(fr.args, un.tile, lds, draw); break;
+        case 6: form_tile<2, DT, true, false, 2>(fr.args, un.tile, lds, draw); break;
+        case 7: form_tile<3, DT, true, false, 1>(fr.args, un.tile, lds, draw); break;
+        case 8: form_tile<3, DT, true, false, 2>(fr.args, un.tile, lds, draw); break;
+        case 9: form_tile<4, DT, true, false, 1>(fr.args, un.tile, lds, draw); break;
+        case 10: form_tile<4, DT, true, false, 2>(fr.args, un.tile, lds, draw); break;
+        case 11: form_tile<5, DT, true, false, 1>(fr.args, un.tile, lds, draw); break;
+        case 12: form_tile<5, DT, true, false, 2>(fr.args, un.tile, lds, draw); break;
+        case 13: form_tile<6, DT, true, false, 1>(fr.args, un.tile, lds, draw); break;
+        case 14: form_tile<6, DT, true, false, 2>(fr.args, un.tile, lds, draw); break;
         }
-    });
+        if (!draws || r == 0) {
+            u = run.unit(++r);
+            continue;
+        }
+        __syncthreads();                   // the unit's readers of the LDS are done
+        if (threadIdx.x == 0) {
+            *number = drawn;
+            if (drawn == run.n - fixed + run.g - 1)   // every unit drawn, and g failures
+                __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        u = fixed + __builtin_amdgcn_readfirstlane(*number);
+        __syncthreads();                   // and the number is read
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1507,7 +1544,7 @@ int launch_batch(int kind, const BatchHeader* hdr, const BatchFrame* frames, con
                  bool compensated, int64_t lds_bytes, void* stream)
 {
     const void* fn = batch_kernel(kind, compensated);
-    if (!fn)
+    if (!fn || kind >= kOrderKinds)
         return (int)hipErrorInvalidValue;
     void* args[] = {(void*)&hdr, (void*)&frames, (void*)&units};
     return (int)hipLaunchKernel(fn, dim3(grid), dim3(kBlock), args, (size_t)lds_bytes,

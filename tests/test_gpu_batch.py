@@ -412,5 +412,22 @@ def test_launches_of_one_list_overlap_on_several_streams(hd):
         torch.cuda.synchronize()
         check("launch", (bt.launch, streams[0]))
         check("replay", (bt.replay, streams[1]))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        bt.launch()
+
+    def captured(stream):
+        with torch.cuda.stream(stream):
+            graph.replay()
+
+    for rep in range(4):
+        say("a captured launch beside others, round %d" % rep)
+        torch.cuda.synchronize()
+        busy @ busy
+        for i in range(6):
+            (captured if i % 2 else bt.launch)(stream=streams[i % 3])
+        torch.cuda.synchronize()
+        check("captured", (captured, streams[2]))
+        check("launch after it", (bt.launch, streams[0]))
     bt.close()
     plan.close()
