@@ -313,9 +313,11 @@ hodmas_status hodmas_batch_set(hodmas_batch_t batch, const hodmas_plan_t* plans,
                                float* const* images, int32_t n_frames, void* stream);
 
 /* Run the current work list on `stream`: one launch per kind
- * present (kind = order x storage type x mirror pairing; unweighted,
- * compensated frames of one storage type whose kinds would each leave the
- * device half empty run as one mixed kind). */
+ * present.  A kind is an order x storage type x mirror pairing x coherence
+ * weighting; the unweighted, compensated kinds of one storage type, two or more,
+ * run as one mixed kind, except those whose LDS would hold most of a long list
+ * to fewer workgroups, and kinds of short units that fill the device by
+ * themselves. */
 hodmas_status hodmas_batch_launch(hodmas_batch_t batch, void* stream);
 
 /* Build (once) a HIP graph holding the kernels of the kinds in the

@@ -157,6 +157,82 @@ void deal_frames(Unit* run, int n, int used, int32_t* cut, std::vector<Unit>& de
     std::copy(dealt.begin(), dealt.end(), run);
 }
 
+// Joins the unweighted kinds of a storage type, where there are two or more, to
+// its mixed kind: one kernel and one tail instead of each kind's.  In us, mixed and
+// apart (launched; replayed as a graph, whose nodes cost more): two frames of 256 x
+// 256 from 64 elements at orders 2 and 3 13.8 and 17.0 (20.6 and 42.3); 18 paired
+// of 128 x 128 at six orders 33 and 50 (40 and 88); 24 paired of 512 x 512 from 128
+// elements 350 and 396 (357 and 389); 24 unpaired of 768 x 768 924 and 1063 (931
+// and 1069).  Left apart are
+// - kinds whose LDS would hold the workgroups of half of the work (by cost) or more
+//   to fewer per CU, in lists that fill the device more than kLong times, where
+//   that decides: 48 frames of 512 x 512 with 7 KB tiles and one of 256 x 256 with
+//   36 KB, all mixed 567 (575), its kind apart 532 (527); 24 of 512 x 512 with 14
+//   KB, which fill it 8 times, 212 (218) and 220 (245).
+// - two kinds of short units that fill it once: the kinds' own kernels hold seven
+//   workgroups instead of six and switch nothing between units (24 frames of 256 x
+//   256 at orders 2 and 3 85 mixed and 78; replayed 91 and 95).
+// - any number of short unpaired kinds each of which fills it kManyFills times: the
+//   tails are small by then (192 of 128 x 128 at six orders, and one with 36 KB
+//   whose kind is apart, 252 mixed and 250; replayed 261 and 250).
+void mix_kinds(std::vector<Unit>& units, int64_t (&lds)[hodmas::kBatchKinds], int cus)
+{
+    constexpr int kMixedPerCu = 6;                   // workgroups of the mixed kernel its registers allow
+    constexpr int64_t kLong = 12, kManyFills = 5;    // times what the device holds at once
+    constexpr int64_t kShortUnit = 500000;           // slots
+    int64_t count[hodmas::kOrderKinds] = {}, cost[hodmas::kOrderKinds] = {};
+    for (const Unit& u : units) {
+        ++count[u.kind];
+        cost[u.kind] += u.cost;
+    }
+    bool joins[hodmas::kOrderKinds] = {};
+    for (int dt = 0; dt < 3; ++dt) {
+        // the mixed kernel's workgroups per CU at each kind's LDS (0: not of this type)
+        int per_cu[hodmas::kOrderKinds] = {};
+        int64_t n = 0, total = 0, no_more[kMixedPerCu + 1] = {};
+        for (int kind = 0; kind < hodmas::kOrderKinds; ++kind) {
+            if (!count[kind] || hodmas::kind_dtype(kind) != dt || hodmas::kind_cf(kind))
+                continue;
+            per_cu[kind] = (int)std::min<int64_t>(kMixedPerCu, std::max<int64_t>(1, hodmas::kMaxLdsBytes / lds[kind]));
+            n += count[kind];
+            total += cost[kind];
+            for (int w = per_cu[kind]; w <= kMixedPerCu; ++w)
+                no_more[w] += cost[kind];
+        }
+        // half of the work or more is in kinds that leave room for `least`
+        int least = 1;
+        while (least < kMixedPerCu && 2 * no_more[least] <= total)
+            ++least;
+        const int64_t fill = (int64_t)least * cus;
+        if (n <= kLong * fill)
+            least = 1;
+        int members = 0, pairing = 1;
+        int64_t fewest = 0, member_cost = 0, member_units = 0;
+        for (int kind = 0; kind < hodmas::kOrderKinds; ++kind) {
+            if (per_cu[kind] < least)
+                continue;
+            fewest = members++ ? std::min(fewest, count[kind]) : count[kind];
+            pairing = std::max(pairing, hodmas::kind_pairing(kind));
+            member_cost += cost[kind];
+            member_units += count[kind];
+        }
+        const bool fills = members == 2 ? member_units > 4 * cus : pairing == 1 && fewest >= kManyFills * fill;
+        if (members < 2 || (member_cost < kShortUnit * member_units && fills))
+            continue;
+        const int mixed = hodmas::mixed_kind(dt);
+        for (int kind = 0; kind < hodmas::kOrderKinds; ++kind) {
+            if (per_cu[kind] < least)
+                continue;
+            joins[kind] = true;
+            lds[mixed] = std::max(lds[mixed], lds[kind]);
+            lds[kind] = 0;
+        }
+    }
+    for (Unit& u : units)
+        if (joins[u.kind])
+            u.kind = hodmas::mixed_kind(hodmas::kind_dtype(u.kind));
+}
+
 // Workgroups a kind's kernel launches with: one per unit.  The device hands a
 // workgroup out as another ends, which evens out better than fixed shares of a
 // grid that just fills the device.  Measured so, and with fixed shares: one
@@ -338,55 +414,10 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     } catch (const std::bad_alloc&) {
         return HODMAS_ENOMEM;
     }
-    // Kinds of one storage type that come together run as one mixed kind.  Two
-    // kinds of short units are better off as their own kernels, which hold more
-    // waves (eight instead of six) and switch nothing between units: 32 frames
-    // of 128 x 128 at orders 2 and 3 55 us apart and 68 mixed, of 256 x 256 100
-    // and 111; two kinds of longer units (four paired 512 x 512 frames 70 and 66
-    // us launched, 93 and 72 replayed), a list that barely fills the device once
-    // (two paired 128 x 128 frames 23 and 12), and three or more kinds (64 such
-    // frames at four orders 76 and 72, replayed 154 and 78; six at six 49 and 15)
-    // gain or lose little.  Any number of kinds stays apart where each fills the
-    // device several times over with short units and none is paired, whose tail
-    // is then small: 128 unpaired float16 frames of 128 x 128 at four orders (8192
-    // units each) 159 us apart and 183 mixed, 384 at six 461 and 505; 64 (4096
-    // units each) 109 and 100 replayed.  Paired kernels hold the mixed kernel's
-    // six waves at the high orders, and stay mixed (384 such float32 frames 410
-    // and 393).
-    constexpr int64_t kShortUnit = 500000, kOneFill = 1024, kManyFills = 8192;   // slots; units; units
-    if (comp) {
-        for (int dt = 0; dt < 3; ++dt) {
-            auto of_type = [&](int kind) {
-                return kind < hodmas::kOrderKinds && hodmas::kind_dtype(kind) == dt && !hodmas::kind_cf(kind);
-            };
-            int present = 0, pairing = 1;
-            for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
-                if (kl[kind] != 0 && of_type(kind)) {
-                    ++present;
-                    pairing = std::max(pairing, hodmas::kind_pairing(kind));
-                }
-            int64_t n = 0, cost = 0;
-            for (const Unit& u : units) {
-                n += of_type(u.kind);
-                cost += of_type(u.kind) ? u.cost : 0;
-            }
-            const int64_t apart = present == 2 ? kOneFill : kManyFills * present - 1;
-            if (present < 2 || (cost < kShortUnit * n && n > apart && (present == 2 || pairing == 1)))
-                continue;
-            const int mixed = hodmas::mixed_kind(dt);
-            for (Unit& u : units)
-                if (of_type(u.kind))
-                    u.kind = mixed;
-            for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
-                if (of_type(kind)) {
-                    kl[mixed] = std::max(kl[mixed], kl[kind]);
-                    kl[kind] = 0;
-                }
-        }
-    }
+    if (comp)
+        mix_kinds(units, kl, b->cus);
     // Each kind runs with the LDS its own plans need, and with as many
-    // workgroups at once as that LDS lets a CU hold: one large-LDS plan does
-    // not hold every other kind to its occupancy.
+    // workgroups at once as that LDS lets a CU hold.
     int kg[hodmas::kBatchKinds] = {};
     for (int kind = 0; kind < hodmas::kBatchKinds; ++kind) {
         if (kl[kind] == 0)

@@ -431,3 +431,38 @@ def test_launches_of_one_list_overlap_on_several_streams(hd):
         check("launch after it", (bt.launch, streams[0]))
     bt.close()
     plan.close()
+
+
+def test_one_large_plan_leaves_the_others_their_workgroups(hd):
+    """A long list of small plans at all orders and one plan of 36 KB tiles: the
+    large one's order runs by itself, so the device holds as many workgroups of
+    the others as their own LDS allows; every image is bitwise its own launch,
+    launched and replayed, also in a short list, where all orders run as one."""
+    f = ph.make_frame(64, 2048, 128, 128, n_points=5, snr_db=15.0, seed=73)
+    arr = ph.to_fp32(f.rf)
+    rf = torch.from_numpy(arr).cuda()
+    small, big = (hd.Plan(f.geometry, f.grid, arr.shape[1], "f32", max_order=6, tiling=(16, 16, 1, c))
+                  for c in (4, 64))
+    own = {(p, k): p.beamform(rf, k).clone() for p in (small, big) for k in range(1, 7)}
+    bt = hd.Batch(400, 400 * small.info().n_tiles, big.info().lds_bytes)
+    bt.set([big], [rf], [3], [torch.empty((f.grid.nz, f.grid.nx), device="cuda")])
+    alone = bt.info().grid
+    bt.set([small], [rf], [3], [torch.empty((f.grid.nz, f.grid.nx), device="cuda")])
+    assert bt.info().grid > alone
+    for frames in (330, 30):
+        use = [(small, i % 6 + 1) for i in range(frames)] + [(big, 3)]
+        outs = [torch.empty((f.grid.nz, f.grid.nx), device="cuda") for _ in use]
+        bt.set([p for p, _ in use], [rf] * len(use), [k for _, k in use], outs)
+        say("%d frames: %d workgroups at once, %d of the large plan alone" % (frames, bt.info().grid, alone))
+        assert (bt.info().grid > alone) == (frames == 330)
+        bt.capture()
+        for go in (bt.launch, bt.replay, bt.replay):
+            for o in outs:
+                o.fill_(float("nan"))
+            go()
+            torch.cuda.synchronize()
+            for i, (o, u) in enumerate(zip(outs, use)):
+                assert torch.equal(o, own[u]), (frames, go.__name__, i)
+    bt.close()
+    small.close()
+    big.close()
