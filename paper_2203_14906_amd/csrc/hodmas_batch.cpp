@@ -30,6 +30,9 @@ constexpr int kLaunches = 4;      // direct launches of one list with draw count
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
+// How a kind of one order runs: not at all, in the mixed kind or by itself.
+enum class RunsAs : char { none, mixed, apart };
+
 }  // namespace
 
 struct hodmas_batch_s {
@@ -50,6 +53,8 @@ struct hodmas_batch_s {
     int64_t occ_lds[hodmas::kBatchKinds] = {};
     int occ_per_cu[hodmas::kBatchKinds] = {};
     bool draws[3] = {};                   // by storage type: the list's mixed kind draws its units
+    // how the list runs the kinds it has, and how captured launches have run them
+    RunsAs runs_as[hodmas::kOrderKinds] = {}, captured[hodmas::kOrderKinds] = {};
     size_t off_frames = 0, off_units = 0, off_counts = 0, bytes = 0;
     char* d_buf = nullptr;
     char* h_buf = nullptr;           // pinned staging of the work list
@@ -175,7 +180,10 @@ void deal_frames(Unit* run, int n, int used, int32_t* cut, std::vector<Unit>& de
 // - any number of short unpaired kinds each of which fills it kManyFills times: the
 //   tails are small by then (192 of 128 x 128 at six orders, and one with 36 KB
 //   whose kind is apart, 252 mixed and 250; replayed 261 and 250).
-void mix_kinds(std::vector<Unit>& units, int64_t (&lds)[hodmas::kBatchKinds], int cus)
+// A kind that a captured launch has run mixed, or apart, stays so in every later
+// list: the capture holds that kernel and no other.
+void mix_kinds(std::vector<Unit>& units, int64_t (&lds)[hodmas::kBatchKinds], int cus,
+               const RunsAs (&captured)[hodmas::kOrderKinds])
 {
     constexpr int kMixedPerCu = 6;                   // workgroups of the mixed kernel its registers allow
     constexpr int64_t kLong = 12, kManyFills = 5;    // times what the device holds at once
@@ -217,15 +225,17 @@ void mix_kinds(std::vector<Unit>& units, int64_t (&lds)[hodmas::kBatchKinds], in
             member_units += count[kind];
         }
         const bool fills = members == 2 ? member_units > 4 * cus : pairing == 1 && fewest >= kManyFills * fill;
-        if (members < 2 || (member_cost < kShortUnit * member_units && fills))
-            continue;
+        const bool mixes = members >= 2 && !(member_cost < kShortUnit * member_units && fills);
         const int mixed = hodmas::mixed_kind(dt);
         for (int kind = 0; kind < hodmas::kOrderKinds; ++kind) {
-            if (per_cu[kind] < least)
+            if (!per_cu[kind])
                 continue;
-            joins[kind] = true;
-            lds[mixed] = std::max(lds[mixed], lds[kind]);
-            lds[kind] = 0;
+            joins[kind] = captured[kind] == RunsAs::none ? mixes && per_cu[kind] >= least
+                                                         : captured[kind] == RunsAs::mixed;
+            if (joins[kind]) {
+                lds[mixed] = std::max(lds[mixed], lds[kind]);
+                lds[kind] = 0;
+            }
         }
     }
     for (Unit& u : units)
@@ -414,8 +424,14 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     } catch (const std::bad_alloc&) {
         return HODMAS_ENOMEM;
     }
+    RunsAs runs_as[hodmas::kOrderKinds];
+    for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
+        runs_as[kind] = kl[kind] ? RunsAs::apart : RunsAs::none;
     if (comp)
-        mix_kinds(units, kl, b->cus);
+        mix_kinds(units, kl, b->cus, b->captured);
+    for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
+        if (runs_as[kind] != RunsAs::none && !kl[kind])
+            runs_as[kind] = RunsAs::mixed;
     // Each kind runs with the LDS its own plans need, and with as many
     // workgroups at once as that LDS lets a CU hold.
     int kg[hodmas::kBatchKinds] = {};
@@ -509,6 +525,7 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     }
     std::memcpy(b->begin, hdr->begin, sizeof(b->begin));
     std::memcpy(b->end, hdr->end, sizeof(b->end));
+    std::memcpy(b->runs_as, runs_as, sizeof(runs_as));
     std::memcpy(b->kind_lds, kl, sizeof(kl));
     std::memcpy(b->kind_grid, kg, sizeof(kg));
     for (int32_t f = 0; f < n_frames; ++f) {
@@ -566,6 +583,10 @@ hodmas_status hodmas_batch_launch(hodmas_batch_t b, void* stream)
     if (!captured) {
         ok = finish(run, st) && ok;
         b->next_run = (turn + 1) % kLaunches;
+    } else if (ok) {
+        for (int kind = 0; kind < hodmas::kOrderKinds; ++kind)
+            if (b->runs_as[kind] != RunsAs::none)
+                b->captured[kind] = b->runs_as[kind];
     }
     if (!ok) {
         (void)hipGetLastError();

@@ -466,3 +466,36 @@ def test_one_large_plan_leaves_the_others_their_workgroups(hd):
     bt.close()
     small.close()
     big.close()
+
+
+@pytest.mark.parametrize("first,then", [(4, 40), (40, 4)])
+def test_a_captured_launch_forms_later_lists(hd, first, then):
+    """A launch captured into a graph of the caller's reads the list from device
+    memory: after a set of more or fewer frames at the same orders, few enough to
+    run as one kernel or enough for one per order, its replays form that list."""
+    f = ph.config_frame(1)
+    arr = ph.to_fp32(f.rf)
+    rf = torch.from_numpy(arr).cuda()
+    plan = hd.Plan(f.geometry, f.grid, arr.shape[1], "f32", max_order=3, tiling=(16, 16, 1, 16))
+    own = {k: plan.beamform(rf, k).clone() for k in (2, 3)}
+    outs = [torch.empty((f.grid.nz, f.grid.nx), device="cuda") for _ in range(40)]
+    bt = hd.Batch(40, 40 * plan.info().n_tiles, plan.info().lds_bytes)
+
+    def put(n):
+        bt.set([plan] * n, [rf] * n, [2 + i % 2 for i in range(n)], outs[:n])
+
+    put(first)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        bt.launch()
+    for n in (first, then, first):
+        put(n)
+        for go in (graph.replay, bt.launch, graph.replay):
+            for o in outs:
+                o.fill_(float("nan"))
+            go()
+            torch.cuda.synchronize()
+            for i in range(n):
+                assert torch.equal(outs[i], own[2 + i % 2]), (n, i)
+    bt.close()
+    plan.close()
