@@ -329,9 +329,10 @@ hodmas_status hodmas_batch_launch(hodmas_batch_t batch, void* stream);
  * instantiated graph to the current work list: kinds absent from it are
  * switched off and each present kind gets its own LDS size and
  * grid; a kind the graph has no kernel for
- * has the graph rebuilt with every kind seen so far.  When that changes a
- * node, the replay first waits for the previous replay of the graph to
- * finish (host-side); replays of an unchanged kind mix do not wait. */
+ * has the graph rebuilt with every kind seen so far.  Where that would change a
+ * node while the previous replay of the graph still runs, a list's first replay
+ * launches its kernels directly instead, and a later one first waits for that
+ * replay (host-side): set and replay in turn do not wait. */
 hodmas_status hodmas_batch_capture(hodmas_batch_t batch);
 hodmas_status hodmas_batch_replay(hodmas_batch_t batch, void* stream);
 

@@ -78,6 +78,7 @@ struct hodmas_batch_s {
         bool pending = false;
     };
     Run replayed, runs[kLaunches];
+    bool list_replayed = false;      // the current list, by the graph or in its place
     int next_run = 0;
     hodmas_batch_info info{};
 };
@@ -546,6 +547,7 @@ hodmas_status hodmas_batch_set(hodmas_batch_t b, const hodmas_plan_t* plans, con
     }
     b->copy_pending = true;
     b->has_list = true;
+    b->list_replayed = false;
     b->info.n_frames = n_frames;
     b->info.n_units = (int64_t)units.size();
     b->info.pixel_channels = pixch;
@@ -608,7 +610,7 @@ hodmas_status hodmas_batch_launch(hodmas_batch_t b, void* stream)
 // off.  Before each replay the nodes are fitted to the current work list in
 // the instantiated graph itself: a kind that is absent is switched off, and a
 // present kind runs with the LDS its own plans need and the grid of its units
-// (launch_grid).
+// (launch_grid), which differs from list to list.
 namespace {
 
 hipKernelNodeParams node_params(const hodmas_batch_s* b, int kind, int grid, int64_t lds, KernelArgs& args)
@@ -694,7 +696,16 @@ hodmas_status hodmas_batch_replay(hodmas_batch_t b, void* stream)
                  (n > 0 && (launch_grid(b, kind, kind_draws(b, kind)) != b->node_grid[kind] ||
                             kind_draws(b, kind) != b->node_draws[kind] || b->kind_lds[kind] != b->node_lds[kind]));
     }
+    const bool first = !b->list_replayed;
+    b->list_replayed = true;
     if ((change || missing) && b->replayed.pending) {
+        // ... so a list's first replay runs its kernels directly while one is:
+        // a loop of sets and replays then never waits for the GPU.  (Fitting a
+        // graph pays from the list's second replay on.)
+        if (first && hipEventQuery(b->replayed.done) == hipErrorNotReady) {
+            (void)hipGetLastError();
+            return hodmas_batch_launch(b, stream);
+        }
         if (hipEventSynchronize(b->replayed.done) != hipSuccess) {
             (void)hipGetLastError();
             return HODMAS_EDEVICE;

@@ -499,3 +499,54 @@ def test_a_captured_launch_forms_later_lists(hd, first, then):
                 assert torch.equal(outs[i], own[2 + i % 2]), (n, i)
     bt.close()
     plan.close()
+
+
+def test_set_and_replay_in_turn_do_not_wait(hd):
+    """Replays of lists that differ in length, order, LDS and kinds while the one
+    before still waits for the GPU: none waits on the host, and each forms its own
+    list; a list replayed again is fitted into the graph."""
+    f = ph.config_frame(1)
+    arr = ph.to_fp32(f.rf)
+    rf = torch.from_numpy(arr).cuda()
+    a, b = (hd.Plan(f.geometry, f.grid, arr.shape[1], "f32", max_order=4, tiling=(16, 16, 1, c)) for c in (16, 64))
+    own = {(p, k): p.beamform(rf, k).clone() for p in (a, b) for k in (2, 4)}
+    outs = [torch.empty((f.grid.nz, f.grid.nx), device="cuda") for _ in range(60)]
+    bt = hd.Batch(60, 60 * a.info().n_tiles, b.info().lds_bytes)
+    busy = torch.randn((8192, 8192), device="cuda")
+    lists = [[(a, 2)] * 60, [(a, 2)] * 31, [(b, 2)] * 60, [(a, 4)] * 7, [(a, 2), (b, 4)] * 30]
+
+    def put(use):
+        bt.set([p for p, _ in use], [rf] * len(use), [k for _, k in use], outs[: len(use)])
+
+    def check(use):
+        torch.cuda.synchronize()
+        for i, u in enumerate(use):
+            assert torch.equal(outs[i], own[u]), i
+
+    put(lists[0])
+    bt.capture()
+    bt.replay()
+    for before, use in zip(lists, lists[1:]):
+        say("%d frames after %d" % (len(use), len(before)))
+        put(before)
+        bt.replay()
+        bt.replay()
+        check(before)
+        for o in outs:
+            o.fill_(float("nan"))
+        done = torch.cuda.Event()
+        for _ in range(20):
+            busy @ busy
+        done.record()
+        bt.replay()                     # `before`, unchanged: behind the products
+        put(use)
+        bt.replay()
+        assert not done.query(), "waited for the GPU"
+        check(use)
+        for o in outs:
+            o.fill_(float("nan"))
+        bt.replay()
+        check(use)
+    bt.close()
+    a.close()
+    b.close()
