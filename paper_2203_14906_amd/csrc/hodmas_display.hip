@@ -548,7 +548,10 @@ __global__ __launch_bounds__(kDispBlock) void log_compress_kernel(DisplayImages 
     for (int w = 0; w < kDispBlock / 64; ++w)
         peak = fmaxf(peak, part[w]);
     const float floor_db = -dyn_range_db;
-    const float inv_peak = peak > 0.f ? 1.f / peak : 0.f;
+    // a peak below the normal numbers, whose reciprocal may overflow, and its
+    // pixels are scaled by a power of two first
+    const float up = peak < 0x1p-126f ? 0x1p100f : 1.f;
+    const float inv_peak = peak > 0.f ? 1.f / (peak * up) : 0.f;
     // four pixels per lane where both buffers are aligned for it
     const bool wide = ((reinterpret_cast<uintptr_t>(env) | reinterpret_cast<uintptr_t>(db)) & 15) == 0;
     const int64_t step = (int64_t)gridDim.x * kDispBlock;
@@ -557,11 +560,11 @@ __global__ __launch_bounds__(kDispBlock) void log_compress_kernel(DisplayImages 
     for (int64_t i = first; i < quads; i += step) {
         const float4 e = reinterpret_cast<const float4*>(env)[i];
         reinterpret_cast<float4*>(db)[i] =
-            make_float4(decibels(e.x, inv_peak, floor_db), decibels(e.y, inv_peak, floor_db),
-                        decibels(e.z, inv_peak, floor_db), decibels(e.w, inv_peak, floor_db));
+            make_float4(decibels(e.x * up, inv_peak, floor_db), decibels(e.y * up, inv_peak, floor_db),
+                        decibels(e.z * up, inv_peak, floor_db), decibels(e.w * up, inv_peak, floor_db));
     }
     for (int64_t i = 4 * quads + first; i < count; i += step)
-        db[i] = decibels(env[i], inv_peak, floor_db);
+        db[i] = decibels(env[i] * up, inv_peak, floor_db);
 }
 
 // ---------------------------------------------------------------------------

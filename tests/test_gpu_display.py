@@ -196,3 +196,22 @@ def test_a_column_that_is_not_finite_stays_alone(hd, nz, bad):
     g = hurt[:, 5].cpu().numpy().astype(np.float64)
     assert np.linalg.norm(g - o[:, 5]) <= TOL_ENV * np.linalg.norm(o[:, 5])
     disp.close()
+
+
+@pytest.mark.parametrize("scale", [1e-36, 1e-38, 1e-39])
+def test_images_at_the_smallest_numbers(hd, scale):
+    """A peak around and below the smallest normal number: no pixel above 0 dB, and
+    the brightest 20 dB within 0.01 dB of the oracle (63 products and sums, each
+    rounded to half of 1.4e-45, are 4.5e-4 of a pixel 20 dB below a peak of 1e-39:
+    0.004 dB)."""
+    nx, nz, dz = 24, 256, 0.075e-3
+    img = (np.random.default_rng(5).standard_normal((nz, nx)) * scale).astype(np.float32)
+    disp = hd.Display(nx, nz, dz, 1540.0, 2e6, 8e6, 63, 60.0)
+    _, db = disp.run(torch.from_numpy(img).cuda())
+    g = db.cpu().numpy().astype(np.float64)
+    _, _, o = D.display(img.astype(np.float64), dz, 1540.0, 2e6, 8e6, 63, 60.0)
+    assert np.all(np.isfinite(g)) and g.max() <= 1e-3 and g.min() >= -60.0
+    bright = o > -20.0
+    say("scale %.0e: worst %.1e dB" % (scale, np.abs(g - o)[bright].max()))
+    assert np.abs(g - o)[bright].max() <= 0.01
+    disp.close()
