@@ -118,16 +118,17 @@ __global__ __launch_bounds__(kMetBlock) void metrics_extent_kernel(const float* 
     for (int i = first; i < 2 * bins; i += step)
         s->hist[i / bins][i % bins] = 0u;
     Extent e = nothing(nt);
-    for (int q = first; q < nt; q += step) {
-        const double v = img[tr.at(q, nx)];
+    // 64 bits: a step past the last pixel of a large region passes 2^31
+    for (int64_t q = first; q < nt; q += step) {
+        const double v = img[tr.at((int)q, nx)];
         e.sum_t += v;
         if (v > e.max_t || (v == e.max_t && e.first == nt)) {
             e.max_t = v;
-            e.first = q;
+            e.first = (int)q;
         }
     }
-    for (int q = first; q < nb; q += step) {
-        const double v = img[br.at(q, nx)];
+    for (int64_t q = first; q < nb; q += step) {
+        const double v = img[br.at((int)q, nx)];
         e.sum_b += v;
         e.max_b = fmax(e.max_b, v);
     }
@@ -158,11 +159,11 @@ __global__ __launch_bounds__(kMetBlock) void metrics_histogram_kernel(const floa
     __syncthreads();
     auto bin = [&](double v) { return min(max((int)(v / peak * bins), 0), bins - 1); };
     if (peak > 0.0)
-        for (int q = first; q < nt; q += step)
-            atomicAdd(&hist[0][bin(img[tr.at(q, nx)])], 1u);
+        for (int64_t q = first; q < nt; q += step)
+            atomicAdd(&hist[0][bin(img[tr.at((int)q, nx)])], 1u);
     double dev = 0.0;
-    for (int q = first; q < nb; q += step) {
-        const double v = img[br.at(q, nx)], d = v - mu_out;
+    for (int64_t q = first; q < nb; q += step) {
+        const double v = img[br.at((int)q, nx)], d = v - mu_out;
         dev += d * d;
         if (peak > 0.0)
             atomicAdd(&hist[1][bin(v)], 1u);

@@ -119,3 +119,19 @@ def test_evaluations_from_many_threads(hd):
         th.join()
     for i in range(n):
         assert all(g == alone[i] for g in got[i]), i
+
+
+def test_regions_of_almost_2_to_the_31_pixels(hd):
+    """65536 pixels fewer than 2^31, in both regions: the last pixel, twice the
+    others, is the maximum, found and counted once."""
+    nz, nx = 32767, 65536
+    n = nz * nx
+    img = torch.ones((nz, nx), device="cuda")
+    img[-1, -1] = 2.0
+    whole = (0, nx, 0, nz)
+    got = hd.image_metrics(img, 1e-4, whole, whole, 64)
+    mu, sigma = 1.0 + 1.0 / n, np.sqrt((1.0 - 1.0 / n) / n)
+    want = {"mu_in": mu, "mu_out": mu, "sigma_out": sigma, "snr_db": 20 * np.log10(mu / sigma), "cr_db": 0.0,
+            "gcnr": 0.0, "fwhm_m": 1e-4}
+    for k, v in want.items():
+        assert got[k] == pytest.approx(v, rel=1e-9, abs=1e-12), k
