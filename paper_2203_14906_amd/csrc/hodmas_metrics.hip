@@ -268,6 +268,8 @@ class Workspace {
                     hipHostMalloc((void**)&host, sizeof(hodmas_metrics) * kSlots, hipHostMallocPortable) == hipSuccess) {
                     d.scratch = static_cast<Scratch*>(ptr);
                     d.result = host;
+                } else {
+                    (void)hipGetLastError();   // the call's own launches are checked with it
                 }
             }
             for (int i = 0; d.scratch && i < kSlots && slot_ < 0; ++i) {
