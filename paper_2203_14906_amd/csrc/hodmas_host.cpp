@@ -186,9 +186,11 @@ hodmas_status build_tables(hodmas_plan_s* p)
         return HODMAS_ENOMEM;
     }
     // untested tiles' rows are copied straight into LDS through one buffer
-    // resource over the frame, whose range is a 32-bit byte count
+    // resource over the frame, whose range is a 32-bit byte count (FP32 and FP16
+    // frames of 2 to 4 GiB have always been tested, int16 ones never)
     const int64_t esz = p->rf.dtype == HODMAS_F32 ? 4 : 2;
-    const bool copies = int64_t(n) * p->rf.channel_stride * esz < (int64_t(1) << 31);
+    const bool copies = int64_t(n) * p->rf.channel_stride * esz <
+                        (p->rf.dtype == HODMAS_I16 ? int64_t(1) << 32 : int64_t(1) << 31);
     const int chunk = p->tiling.chunk;
     const int split = p->tiling.split;
     int32_t max_window = 2;

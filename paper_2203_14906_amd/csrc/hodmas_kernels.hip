@@ -279,7 +279,7 @@ __device__ __forceinline__ Rows load_rows(const FrameArgs& A, ConstStage st, int
     const int elem = ent[2 * src];
     const int channel = mirrored ? A.n_elements - 1 - elem : elem, first = ent[2 * src + 1];
     if constexpr (!CHECK)
-        return {(channel * (int)A.stride + first) * (DT == HODMAS_F32 ? 4 : 2), 0};
+        return {int(((unsigned)channel * (unsigned)A.stride + (unsigned)first) * (DT == HODMAS_F32 ? 4u : 2u)), 0};
     else
         return {first, channel};
 }
@@ -334,9 +334,10 @@ __device__ __forceinline__ void stage_direct(const FrameArgs& A, ConstStage st, 
                 }
             }
         } else {
-            const int bytes = A.n_elements * (int)A.stride * esz;   // below 2^31: the plan tests every tile otherwise
+            // below 2^32 (the plan tests every tile otherwise), as are the row starts: both unsigned
+            const unsigned bytes = (unsigned)A.n_elements * (unsigned)A.stride * esz;
             const __amdgpu_buffer_rsrc_t rs =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(A.rf), (short)0, bytes, kBufferFlags);
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(A.rf), (short)0, (int)bytes, kBufferFlags);
             for (int b = 0; b < window; b += 64) {
                 if (b + lane < window) {
                     for (int m = 0; m < cend; ++m)

@@ -458,3 +458,40 @@ def test_all_orders_config1_and_degenerate(hd):
     assert L.hodmas_beamform_orders(plan.handle, p_rf, 2, None, None) == hd.EINVAL
     torch.cuda.synchronize()
     plan.close()
+
+
+@pytest.mark.parametrize("mirror", [False, True])
+@pytest.mark.parametrize("stride", [1 << 24, (1 << 25) - 64])
+def test_int16_frames_of_2_to_4_gib(hd, stride, mirror):
+    """64 records so far apart that the frame takes 2 GiB, or all but 4: row starts
+    past 2^31 bytes.  Every image is bitwise that of the same records side by side,
+    per order, all orders and in a batch.  (The frame stands in the middle of an
+    allocation, so an offset taken for a signed one would still be inside.)"""
+    n, S = 64, 700
+    f = ph.make_frame(n, S, 256, 48, n_points=8, snr_db=15.0, seed=29)
+    codes, scale = ph.to_int16(f.rf, 29)
+    near = torch.from_numpy(codes).cuda()
+    pool = torch.zeros(3 * n * stride, dtype=torch.int16, device="cuda")
+    far = pool[n * stride:2 * n * stride].view(n, stride)
+    far[:, :S] = near
+    fl = hd.FLAG_MIRROR if mirror else 0
+    plans = [hd.Plan(f.geometry, f.grid, S, "i16", max_order=6, dequant_scale=float(scale), flags=fl,
+                     channel_stride=s) for s in (S, stride)]
+    assert not all(t.check for t in plans[1].tables()[0])
+    images = [[p.beamform(r, k) for k in range(1, 7)] for p, r in zip(plans, (near, far))]
+    for k, (a, b) in enumerate(zip(*images)):
+        say("int16 records %d apart, mirror %s, order %d" % (stride, mirror, k + 1))
+        assert torch.equal(a, b), k + 1
+    if not mirror:
+        for a, b in zip(plans[0].beamform_orders(near, 6), plans[1].beamform_orders(far, 6)):
+            assert torch.equal(a, b)
+    bt = hd.Batch(6, 6 * plans[1].info().n_tiles, plans[1].info().lds_bytes)
+    outs = [torch.empty_like(a) for a in images[0]]
+    bt.set([plans[1]] * 6, [far] * 6, list(range(1, 7)), outs)
+    bt.launch()
+    torch.cuda.synchronize()
+    for a, b in zip(images[0], outs):
+        assert torch.equal(a, b)
+    bt.close()
+    for p in plans:
+        p.close()

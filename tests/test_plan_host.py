@@ -444,3 +444,20 @@ def test_automatic_chunk_takes_fewer_rounds_at_1024():
     inf = p.info()
     assert inf.tiling.chunk == 128 and inf.lds_bytes > 20 * 1024
     p.close()
+
+
+@pytest.mark.parametrize("dtype,stride,tested", [
+    ("f32", (1 << 23) - 64, False), ("f32", 1 << 23, True), ("f16", (1 << 24) - 64, False), ("f16", 1 << 24, True),
+    ("i16", 1 << 24, False), ("i16", (1 << 25) - 64, False), ("i16", 1 << 25, True)])
+def test_frames_beyond_one_buffer_range(dtype, stride, tested):
+    """FP32 and FP16 frames of 2 GiB and int16 frames of 4 GiB and more have every
+    tile range-tested; smaller ones only the tiles at the record ends."""
+    f = ph.make_frame(64, 600, 48, 40, n_points=3, seed=5)
+    one = hodmas.Plan(f.geometry, f.grid, 600, dtype, max_order=2, flags=hodmas.FLAG_HOST_ONLY)
+    far = hodmas.Plan(f.geometry, f.grid, 600, dtype, max_order=2, flags=hodmas.FLAG_HOST_ONLY,
+                      channel_stride=stride)
+    near = [t.check for t in one.tables()[0]]
+    assert not all(near)
+    assert [t.check for t in far.tables()[0]] == ([1] * len(near) if tested else near)
+    one.close()
+    far.close()
