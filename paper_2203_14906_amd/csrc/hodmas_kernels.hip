@@ -970,7 +970,10 @@ void hodmas_batch_kernel(const BatchHeader* __restrict__ hdr, const BatchFrame* 
 {
     extern __shared__ float lds[];
     const UnitRun run = unit_run(hdr, batch_kind(K, DT, M, CF ? 1 : 0));
-    for (int r = 0, u = run.l; u < run.n; u = run.unit(++r)) {
+    for (int r = 0; r * run.g < run.n; ++r) {
+        const int u = run.unit(r);
+        if (u >= run.n)
+            continue;
         const BatchUnit un = load_const(units, run.first + u);
         const BatchFrame fr = load_const(frames, un.frame);
         form_tile<K, DT, COMP, CF, M>(fr.args, un.tile, lds);
