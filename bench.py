@@ -3,7 +3,7 @@
 
 Workload (default): 128-element array, 2048 samples per channel, 512 x 512
 grid, float32 RF, orders k = 1..6.  A step beamforms a batch of B resident
-frames (distinct seeds, already in HBM) at every order: one persistent batched
+frames (distinct seeds, already in HBM) at every order: one batched
 launch per order over the B frames (--per-frame-step: B x 6 per-frame
 launches), with mirror pairs -- the array and the grid are symmetric about
 x = 0, so one workgroup forms a tile and its mirror image from one set of
@@ -66,7 +66,7 @@ def parse():
     ap.add_argument("--workload", default="plain", choices=["plain", "small", "reduced", "batch", "serve", "display"],
                     help="plain: 128 el / 512^2 / FP32 (default); small: 64 el / 128^2 / FP32 latency and "
                          "back-to-back throughput; reduced: 256 el / 1024^2 / int16+FP16; "
-                         "batch: 256 mixed FP16 frames in one persistent launch vs 256 FP32 launches; "
+                         "batch: 256 mixed FP16 frames in one batched launch vs 256 FP32 launches; "
                          "serve: Poisson arrivals, continuous batching vs plain FP32 per request; "
                          "display: band-pass + Hilbert envelope + log compression of beamformed images")
     ap.add_argument("--rates", default="500,1000,2000", help="serve: arrival rates (frames/s)")
@@ -191,7 +191,7 @@ def bench_plain(args, torch):
     pixch = grid.nx * grid.nz * n_el
 
     # A step beamforms the B resident frames at every order.  By default each
-    # order is one persistent batched launch over the B frames (their work
+    # order is one batched launch over the B frames (their work
     # lists are built here, outside the timed region; workgroups drift out of
     # step, so one tile's staging overlaps another's arithmetic and the
     # frames' tails overlap); --per-frame-step runs B per-frame launches per
@@ -405,7 +405,7 @@ def bench_plain(args, torch):
         "data": "synthetic",
         "config": {"workload": "plain HO-DMAS, 128-element array, 2048 samples/channel, 512x512 grid, "
                                "FP32 RF, orders 1-6, %d resident frames per step, %s%s" % (
-                                   args.batch, "each order one persistent batched launch over the frames"
+                                   args.batch, "each order one batched launch over the frames"
                                    if batched_step else "one launch per frame and order",
                                    ", mirror pairs" if mplan is not None else ""),
                    "n_elements": n_el, "n_samples": S, "grid": [grid.nx, grid.nz],
@@ -493,7 +493,7 @@ def bench_small(args, torch):
     A frame is about a microsecond of GPU work, so one launch is bound by launch
     overhead: report single-launch latency (host wall clock of launch plus
     synchronize, and the kernel's own time from HIP events) and throughput over
-    1024 back-to-back frames, as per-frame launches and as one persistent batch
+    1024 back-to-back frames, as per-frame launches and as one batched
     launch (unpaired and with mirror pairs; the batch plans take the tiling the
     autotuner picks for batches, and the graph replay is timed beside the
     direct launch)."""
@@ -573,7 +573,7 @@ def bench_small(args, torch):
                "kernel_us_p50": round(kern[len(kern) // 2], 2),
                "back_to_back_us_per_frame": round(b2b_ms * 1e3 / n_frames, 3),
                "back_to_back_gpixch_s": round(pixch * n_frames / (b2b_ms * 1e-3) / 1e9, 2)}
-        # the same frames as one persistent launch, with the tiling the
+        # the same frames as one batched launch, with the tiling the
         # autotuner picks for batches (timed as a batch runs them), and with
         # the plan's default tiling (made for a single frame) for comparison
         for name, flags in (("batched", 0), ("batched_mirror_pairs", hodmas.FLAG_MIRROR),
@@ -692,7 +692,7 @@ def bench_batch(args, torch):
 
 def batch_workload(args, torch):
     """256 mixed frames (N, S, grid side, order drawn per frame; FP16 RF) in one
-    persistent launch replayed from a HIP graph, with mirror pairs (--no-mirror:
+    batched launch replayed from a HIP graph, with mirror pairs (--no-mirror:
     unpaired), against 256 plain per-frame FP32 launches on one stream.  All frames are submitted at t = 0; latency is
     each frame's completion time."""
     import numpy as np
@@ -742,7 +742,7 @@ def batch_workload(args, torch):
         a, b = ob.double(), op.double()
         worst = max(worst, float(torch.linalg.norm(a - b) / torch.linalg.norm(b).clamp_min(1e-300)))
     inf = batch.info()
-    res = {"metric": "frames/s and p99 latency, batched (one persistent launch) vs plain per-frame FP32",
+    res = {"metric": "frames/s and p99 latency, batched (one launch) vs plain per-frame FP32",
            "unit": "frames/s", "n_gpus": 1, "data": "synthetic", "dtype": "f16 storage / f32 compute",
            "config": {"workload": "256 mixed frames: N in {64,128,256}, S in {1024,2048,4096}, "
                                   "grid side in {256,512,768,1024}, order 1..6, seed 4000",

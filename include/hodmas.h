@@ -214,9 +214,11 @@ const char* hodmas_status_string(hodmas_status status);
  * keyed by device architecture and every input that changes the plan.
  * With HODMAS_FLAG_TUNE_BATCH (unless HODMAS_FLAG_CF comes with
  * HODMAS_FLAG_ACC_PLAIN, which no batch runs) each candidate is timed
- * the way a batch runs it: copies of the frame, each with its own image, in
- * one batched launch of up to 256 copies -- enough work units to
- * fill the device -- and the time per copy is compared.
+ * the way a batch of that order runs it: copies of the frame, each with its own
+ * image, in one batched launch of up to 256 copies -- enough work units to
+ * fill the device -- and the time per copy is compared.  A list of several
+ * orders may run in another kernel (hodmas_batch_launch), which is not timed:
+ * there the tiling chosen so can be slower than the plan's own.
  * Allocates and frees scratch device memory; not for the hot path.
  * Errors: EINVAL, ENOMEM, EDEVICE, EUNSUPPORTED (no candidate could run). */
 hodmas_status hodmas_autotune(const hodmas_geometry* geometry, const hodmas_grid* grid,

@@ -29,8 +29,11 @@ namespace {
 constexpr int64_t kComputeUnits = 256;
 
 // Rounds of workgroups a one-frame launch of `units` tiles needs over the
-// CUs when each takes `lds` bytes of LDS and `block` threads (a CU holds at
-// most 32 waves).
+// CUs when each takes `lds` bytes of LDS and `block` threads, by the 32 waves a
+// CU has room for.  (The kernels hold 28: their 106 scalar registers leave seven
+// waves per SIMD, and 4096 tiles are three rounds then, not two.  What rests on
+// this count -- the chunk of 1024 x 1024 plans, and whether buffers for shared
+// delays pay -- was measured as it stands.)
 int64_t launch_rounds(int64_t units, int64_t lds, int64_t block)
 {
     const int64_t by_waves = std::max<int64_t>(1, 32 / std::max<int64_t>(1, block / 64));

@@ -59,8 +59,7 @@ static_assert(batch_kind(kind_order(kOrderKinds - 1), kind_dtype(kOrderKinds - 1
                   batch_kind(kind_order(40), kind_dtype(40), kind_pairing(40), kind_cf(40)) == 40,
               "kind decoding");
 // ... and one kind per storage type whose kernel forms units of any order and
-// pairing (unweighted, compensated): a work list of several kinds that are
-// each too small to fill the device runs as one.
+// pairing (unweighted, compensated): most work lists of several kinds run as one.
 constexpr int mixed_kind(int dtype) { return kOrderKinds + dtype; }
 constexpr int kBatchKinds = kOrderKinds + 3;
 

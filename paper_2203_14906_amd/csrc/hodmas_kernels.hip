@@ -934,8 +934,9 @@ __global__ __launch_bounds__(kMaxBlock) void hodmas_frame_kernel(FrameArgs A)
 // about equal estimated cost, each sorted by cost); the g workgroups on XCD x
 // (workgroups x, x+8, ...) walk run x, the l-th of them taking unit l.  A grid
 // has one workgroup per unit of the longest run; only in lists beyond the
-// largest grid does the l-th go on to units 2g-1-l, 2g+l, ... (a snake, which
-// evens out the per-workgroup cost).  With
+// largest grid, or beyond the list a captured launch was made for, does the l-th
+// go on to units 2g-1-l, 2g+l, ... (a snake, which evens out the per-workgroup
+// cost).  With
 // M == 2 a unit is a mirror pair, named by its left tile.  Each unit runs
 // exactly the code of the per-frame kernel, so a frame's image does not depend
 // on what else is in the batch.
@@ -1004,7 +1005,7 @@ void hodmas_mixed_kernel(const BatchHeader* __restrict__ hdr, const BatchFrame* 
     const UnitRun run = unit_run(hdr, mixed_kind(DT));
     const int fixed = 2 * run.g;                     // units taken without drawing
     const bool draws = counts != nullptr && run.n > fixed;
-    int* const count = &counts[DT * kXcds + blockIdx.x % kXcds].n;
+    int* const count = draws ? &counts[DT * kXcds + blockIdx.x % kXcds].n : nullptr;
     int* const number = reinterpret_cast<int*>(lds);
     for (int r = 0, u = run.l; u < run.n;) {
         int drawn = 0;
