@@ -16,7 +16,7 @@
 // at the dynamic range.
 //
 // Kernel 1 is bound by VALU issue where the launch fills the device (63 taps:
-// half of its instructions are the filter's) and by one wave's latency where
+// 68 of its 120 VALU instructions per pixel are the filter's) and by one wave's latency where
 // it does not.  16 images of 1024 x 1024, 63 taps: 71 us, and kernel 2 24 us
 // (5.4 TB/s of reads and writes), together 98 us a pass; a radix-2 transform
 // per column with every pass through LDS took 407 + 57 us.  One 512 x 512

@@ -480,8 +480,9 @@ __device__ __forceinline__ float dot4(const float (&a)[4], const float (&b)[4])
 
 // y^1 .. y^K of four elements' signed K-th roots, each power summed over the
 // four.  Bound by VALU issue, so every power that no later power needs is formed
-// inside its sum (dot4): 8.5 instead of 10 instructions per element at K = 6,
-// 6.5 instead of 8 at K = 5, 0.75 fewer at K = 3 and 4.  Measured: int16, 256
+// inside its sum (dot4): counted per element over the whole paired kernels 22.4
+// instead of 23.3 instructions at K = 6, 20.1 instead of 20.8 at K = 5, 0.3 to 0.4
+// fewer at K = 3 and 4 (unpaired 0.2 to 0.6 fewer).  Measured: int16, 256
 // elements, 1024 x 1024, order 6 231.3 -> 225.3 us; float32 mirror pairs, 128
 // elements, 2048 x 2048, order 5 300.6 -> 289.6 us; the six orders of eight
 // 512 x 512 frames 823 -> 802 us.  (Carrying the symmetric sums themselves,
